@@ -28,7 +28,8 @@
  *     is exact.
  *   - dt = LA_BF16: tensors are bfloat16; contractions use bf16 operands with
  *     fp32 accumulation and the running state is kept in fp32.
- *     dt = LA_F32: tensors and all arithmetic are fp32.
+ *     dt = LA_F32: tensors and all sums are fp32; products are those of fp32 operands (formed on
+ *     the matrix cores from exact three-part bf16 splits), never of rounded ones.
  *   - `workspace` is a DEVICE pointer to at least la_workspace_bytes(...)
  *     bytes, 256-byte aligned, owned by the caller; it may be NULL when that
  *     query returns 0.  Its contents are scratch (segment states) and need

@@ -14,7 +14,7 @@
 #include "la_kernels_bf16_dma.h"
 #include "la_kernels_bf16_dma_wide.h"
 #include "la_kernels_f32.h"
-#include "la_kernels_f32m.h"
+#include "la_kernels_f32s.h"
 #include "la_kernels_gate.h"
 #include "la_kernels_lrpe.h"
 #include "la_kernels_misc.h"
@@ -53,7 +53,7 @@ struct Switches {
     std::atomic<long> lseg{0};           // > 0: segment length in tokens
     std::atomic<long> no_pair{0};        // != 0: the dK and dV scans are launched separately
     std::atomic<long> no_decay_skip{0};  // != 0: the segment-state pre-pass reads every block
-    std::atomic<long> f32_plain{0};      // != 0: fp32 at d = 128 runs the FMA kernel
+    std::atomic<long> f32_plain{0};      // != 0: fp32 runs the FMA kernel
     std::atomic<long> store_policy{0};   // direct-to-LDS scan: 2 = ordinary instead of non-temporal result stores
     std::atomic<long> staged_prepass{0}; // != 0: bf16 runs the register-staged segment-state pre-pass
     std::atomic<long> prepass_groups{0}; // 1, 2: wave groups per workgroup of the direct-to-LDS pre-pass (own choice: 4)
@@ -101,7 +101,8 @@ struct Plan {
     int S;          // segments per scan
 };
 
-// Block length of the block-scan kernel la_fwd / la_bwd run (the paper's "block size B").
+// Block length of the block-scan kernel la_fwd / la_bwd run (the paper's "block size B").  fp32 at d = 64
+// is planned in blocks of 64 rows, which its kernel walks as two of 32.
 int tile_len(int d, la_dtype dt)
 {
     if (dt == LA_BF16) return g_sw.staged_scan.load(std::memory_order_relaxed) ? 64 : 32;
@@ -321,17 +322,19 @@ hipError_t launch_f32(const ScanLaunch &a, const LaLambdas &lams, hipStream_t s)
     return hipGetLastError();
 }
 
-template <int D, bool REV, bool STATE_ONLY>
-hipError_t launch_f32m(const ScanLaunch &a, const LaLambdas &lams, hipStream_t s)
+template <int D, bool STATE_ONLY>
+hipError_t launch_f32s(const ScanLaunch &a, const LaLambdas &lams, hipStream_t s)
 {
-    using Cfg = F32mCfg<D>;
-    auto kern = la_scan_f32m<D, REV, STATE_ONLY>;
+    using Cfg = F32sCfg<D>;
+    auto kern = la_scan_f32s<D, STATE_ONLY>;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
-    std::call_once(once, [&] { attr_err = allow_lds(kern, Cfg::lds_bytes); });
+    std::call_once(once, [&] { attr_err = allow_lds(kern, Cfg::lds_bytes(STATE_ONLY)); });
     if (attr_err != hipSuccess) return attr_err;
-    dim3 grid((unsigned)(a.items * a.nroles)), block(Cfg::NT);   // roles one after the other
-    hipLaunchKernelGGL(kern, grid, block, Cfg::lds_bytes, s, a, lams);
+    // several block scans in one launch: items padded to a multiple of the 8 XCDs
+    const unsigned n = (unsigned)a.nroles, items = (unsigned)a.items;
+    dim3 grid(STATE_ONLY || n == 1 ? n * items : n * ((items + 7) / 8 * 8)), block(Cfg::NT);
+    hipLaunchKernelGGL(kern, grid, block, Cfg::lds_bytes(STATE_ONLY), s, a, lams);
     return hipGetLastError();
 }
 
@@ -379,11 +382,12 @@ hipError_t launch_scan_kernel(const ScanLaunch &a, const LaLambdas &lams, int d,
         return d == 64 ? launch_bf16_direct<REV, STATE_ONLY, 64>(a, lams, acts != 0, s)
                        : launch_bf16_direct<REV, STATE_ONLY, 128>(a, lams, acts != 0, s);
     }
-    // fp32: d = 64 runs the literal FMA kernel with 64-row blocks; d = 128 the matrix-core kernel
-    // (32-row blocks; the "f32_plain" switch selects the FMA kernel there too, for comparisons)
-    if (d == 64) return launch_f32<64, 64, REV, STATE_ONLY>(a, lams, s);
-    if (g_sw.f32_plain.load(std::memory_order_relaxed)) return launch_f32<128, 32, REV, STATE_ONLY>(a, lams, s);
-    return launch_f32m<128, REV, STATE_ONLY>(a, lams, s);
+    // fp32: products of three-part bf16 splits on the matrix cores; the "f32_plain" switch selects the
+    // literal FMA kernel, for comparisons
+    if (g_sw.f32_plain.load(std::memory_order_relaxed))
+        return d == 64 ? launch_f32<64, 64, REV, STATE_ONLY>(a, lams, s)
+                       : launch_f32<128, 32, REV, STATE_ONLY>(a, lams, s);
+    return d == 64 ? launch_f32s<64, STATE_ONLY>(a, lams, s) : launch_f32s<128, STATE_ONLY>(a, lams, s);
 }
 
 LaLayout contiguous_layout(int H, int n, int d)
@@ -531,8 +535,9 @@ int run_reverse_pair(const ScanArgs &ak, const ScanArgs &av, const LaLambdas &la
 // Backward pass.  dQ = scan(dO, V, K) is the first loop of Alg. 6 (state KV^T); the
 // second loop is the reverse pair above.  With segments, the two pre-passes (forward
 // states of (V, K), reverse states of (dO, Q)) run as one launch into the two halves
-// of the scratch, then the two segment scans, then the block scans: for bf16 at d = 128
-// without activations all three as the roles of one launch, else dQ's and the pair's.
+// of the scratch, then the two segment scans, then the block scans: for fp32, and for bf16
+// without activations, all three as the roles of one launch, else dQ's and the pair's.  (fp32, two scans
+// of 256 tokens: the three launches took three times as long as the one, 4 us a block either way.)
 // With `swish`, Q and K are pre-activations: they are activated wherever they are an
 // operand, and dQ, dK are multiplied by phi'(Q), phi'(K) as they are stored.
 int run_backward(const void *Q, const void *K, const void *V, const void *dO, void *dQ, void *dK,
@@ -584,14 +589,17 @@ int run_backward(const void *Q, const void *K, const void *V, const void *dO, vo
     }
     const int acts = pre[0].act | pre[1].act | av.act;
     const bool all_ext = pre[0].act == LA_ACT_EXT && pre[1].act == LA_ACT_EXT && av.act == LA_ACT_EXT;
-    if (!g_sw.no_trio.load(std::memory_order_relaxed) && dt == LA_BF16 &&
-        (acts == 0 || all_ext) && !g_sw.staged_scan.load(std::memory_order_relaxed) &&
-        !g_sw.no_pair.load(std::memory_order_relaxed) && !g_sw.ablate.load(std::memory_order_relaxed)) {
+    const bool one_launch = !g_sw.no_trio.load(std::memory_order_relaxed) && !g_sw.no_pair.load(std::memory_order_relaxed) &&
+        (dt == LA_BF16 ? (acts == 0 || all_ext) && !g_sw.staged_scan.load(std::memory_order_relaxed) &&
+                             !g_sw.ablate.load(std::memory_order_relaxed)
+                       : !g_sw.f32_plain.load(std::memory_order_relaxed));
+    if (one_launch) {
         ScanLaunch l;
         l.r[0] = pre[0]; l.r[1] = pre[1]; l.r[2] = av; l.nroles = 3; l.items = (int)(scans * p.S);
         ScopedTimer t(s);
         hipError_t e;
-        if (d == 64) e = all_ext ? launch_bf16_dma_trio<true, 64>(l, lams, s) : launch_bf16_dma_trio<false, 64>(l, lams, s);
+        if (dt == LA_F32) e = d == 64 ? launch_f32s<64, false>(l, lams, s) : launch_f32s<128, false>(l, lams, s);
+        else if (d == 64) e = all_ext ? launch_bf16_dma_trio<true, 64>(l, lams, s) : launch_bf16_dma_trio<false, 64>(l, lams, s);
         else e = all_ext ? launch_bf16_dma_trio<true>(l, lams, s) : launch_bf16_dma_trio<false>(l, lams, s);
         return e == hipSuccess ? LA_OK : LA_ERR_LAUNCH;
     }

@@ -13,8 +13,7 @@
  *                    instead of one XCD-paired launch
  *   "no_decay_skip"  != 0: the segment-state pre-pass reads every block, also those whose
  *                    decay weight is below its cut-off
- *   "f32_plain"      != 0: fp32 at d = 128 runs the plain FMA kernel instead of the
- *                    matrix-core one
+ *   "f32_plain"      != 0: fp32 runs the plain FMA kernel instead of the matrix-core one
  *   "ablate"         1..4: measurement-only variants of the direct-to-LDS block scan that
  *                    leave work out (1: no result stores, 2: loads and barriers only,
  *                    3: arithmetic only, 4: loads, barriers and stores without arithmetic);
