@@ -118,22 +118,45 @@ def _dt(t: torch.Tensor) -> int:
 
 def _check(ts: Sequence[torch.Tensor]):
     t0 = ts[0]
-    if t0.dim() != 4:
+    shape, dtype, device = t0.shape, t0.dtype, t0.device
+    if len(shape) != 4:
         raise ValueError("la: tensors must be [B, H, n, d]")
     for t in ts:
         if not t.is_cuda:
             raise ValueError("la: tensors must live on the GPU")
-        if t.shape != t0.shape or t.dtype != t0.dtype or t.device != t0.device:
+        if t.shape != shape or t.dtype != dtype or t.device != device:
             raise ValueError("la: tensors must share shape, dtype and device")
         if not t.is_contiguous():
             raise ValueError("la: tensors must be contiguous [B, H, n, d]")
 
 
 def _lam(lam, H: int):
-    vals = [float(x) for x in lam]
+    vals = lam if type(lam) in (list, tuple) else list(lam)
     if len(vals) != H:
         raise ValueError("la: lambda must have H entries")
-    return (ctypes.c_float * H)(*vals)
+    try:
+        return (ctypes.c_float * H)(*vals)
+    except TypeError:                       # entries that only float() understands
+        return (ctypes.c_float * H)(*[float(x) for x in vals])
+
+
+# Handle of a device's current stream.  (Through the public Stream object it takes 1.5 us, and entering
+# a torch.cuda.device block another 3: more than the launch of a small kernel.)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+    lambda index: torch.cuda.current_stream(index).cuda_stream)
+
+
+def _launch(entry: str, device: torch.device, *args):
+    """Call a library entry point with `args` and the current stream of `device`, `device` being current."""
+    fn = getattr(load_library(), entry)
+    index = device.index
+    if index == torch.cuda.current_device():
+        rc = fn(*args, _raw_stream(index))
+    else:
+        with torch.cuda.device(device):
+            rc = fn(*args, _raw_stream(index))
+    if rc != 0:
+        raise LaError(rc, entry)
 
 
 def la_workspace_bytes(B: int, H: int, n: int, d: int, dt: int, is_bwd: bool) -> int:
@@ -150,11 +173,11 @@ def la_plan(B: int, H: int, n: int, d: int, dt: int) -> Tuple[int, int, int]:
 
 
 def _workspace(B, H, n, d, dt, is_bwd, device, workspace: Optional[torch.Tensor]):
-    need = la_workspace_bytes(B, H, n, d, dt, is_bwd)
-    if workspace is None and need > 0:
-        workspace = torch.empty(need, dtype=torch.uint8, device=device)
     if workspace is None:
-        return None, 0, 0
+        need = la_workspace_bytes(B, H, n, d, dt, is_bwd)
+        if need == 0:
+            return None, 0, 0
+        workspace = torch.empty(need, dtype=torch.uint8, device=device)
     return workspace, workspace.data_ptr(), workspace.numel() * workspace.element_size()
 
 
@@ -168,12 +191,8 @@ def la_fwd(Q, K, V, lam, O=None, workspace: Optional[torch.Tensor] = None, _entr
         _check([Q, O])
     dt = _dt(Q)
     ws, ws_ptr, ws_bytes = _workspace(B, H, n, d, dt, False, Q.device, workspace)
-    with torch.cuda.device(Q.device):
-        stream = torch.cuda.current_stream().cuda_stream
-        rc = getattr(load_library(), _entry)(Q.data_ptr(), K.data_ptr(), V.data_ptr(), _lam(lam, H),
-                                             O.data_ptr(), B, H, n, d, dt, ws_ptr, ws_bytes, stream)
-    if rc != 0:
-        raise LaError(rc, _entry)
+    _launch(_entry, Q.device, Q.data_ptr(), K.data_ptr(), V.data_ptr(), _lam(lam, H), O.data_ptr(), B, H, n, d,
+            dt, ws_ptr, ws_bytes)
     return O
 
 
@@ -185,12 +204,8 @@ def la_fwd_static(Q, K, V, lam, O):
     O must be given (this wrapper allocates nothing either)."""
     _check([Q, K, V, O])
     B, H, n, d = Q.shape
-    with torch.cuda.device(Q.device):
-        stream = torch.cuda.current_stream().cuda_stream
-        rc = load_library().la_fwd_static(Q.data_ptr(), K.data_ptr(), V.data_ptr(), _lam(lam, H),
-                                          O.data_ptr(), B, H, n, d, _dt(Q), stream)
-    if rc != 0:
-        raise LaError(rc, "la_fwd_static")
+    _launch("la_fwd_static", Q.device, Q.data_ptr(), K.data_ptr(), V.data_ptr(), _lam(lam, H), O.data_ptr(), B, H,
+            n, d, _dt(Q))
     return O
 
 
@@ -208,11 +223,7 @@ def debug_get(name: str) -> int:
 def debug_mfma_rate(workgroups: int, iters: int, sink: torch.Tensor) -> int:
     """Launch the register-only MFMA loop (csrc/la_debug.h) on the current stream; returns the
     number of floating-point operations the launch executes."""
-    with torch.cuda.device(sink.device):
-        stream = torch.cuda.current_stream().cuda_stream
-        rc = load_library().la_debug_mfma_rate(int(workgroups), int(iters), sink.data_ptr(), stream)
-    if rc != 0:
-        raise LaError(rc, "la_debug_mfma_rate")
+    _launch("la_debug_mfma_rate", sink.device, int(workgroups), int(iters), sink.data_ptr())
     return workgroups * 4 * 4 * iters * 2 * 32 * 32 * 16
 
 
@@ -254,12 +265,8 @@ def la_fwd_state(Q, K, V, lam, kv_in=None, kv_out=None, O=None, workspace: Optio
     dt = _dt(Q)
     p_in, p_out = _check_state(kv_in, B, H, d, Q.device), _check_state(kv_out, B, H, d, Q.device)
     ws, ws_ptr, ws_bytes = _workspace(B, H, n, d, dt, False, Q.device, workspace)
-    with torch.cuda.device(Q.device):
-        stream = torch.cuda.current_stream().cuda_stream
-        rc = load_library().la_fwd_state(Q.data_ptr(), K.data_ptr(), V.data_ptr(), _lam(lam, H),
-                                         O.data_ptr(), p_in, p_out, B, H, n, d, dt, ws_ptr, ws_bytes, stream)
-    if rc != 0:
-        raise LaError(rc, "la_fwd_state")
+    _launch("la_fwd_state", Q.device, Q.data_ptr(), K.data_ptr(), V.data_ptr(), _lam(lam, H), O.data_ptr(), p_in,
+            p_out, B, H, n, d, dt, ws_ptr, ws_bytes)
     return O
 
 
@@ -275,12 +282,8 @@ def la_decode_step(q, k, v, lam, kv, o=None):
     p_kv = _check_state(kv, B, H, d, q.device)
     if p_kv == 0:
         raise ValueError("la: kv is required")
-    with torch.cuda.device(q.device):
-        stream = torch.cuda.current_stream().cuda_stream
-        rc = load_library().la_decode_step(q.data_ptr(), k.data_ptr(), v.data_ptr(), _lam(lam, H),
-                                           p_kv, o.data_ptr(), B, H, d, _dt(q), stream)
-    if rc != 0:
-        raise LaError(rc, "la_decode_step")
+    _launch("la_decode_step", q.device, q.data_ptr(), k.data_ptr(), v.data_ptr(), _lam(lam, H), p_kv,
+            o.data_ptr(), B, H, d, _dt(q))
     return o
 
 
@@ -295,13 +298,8 @@ def la_bwd(Q, K, V, lam, dO, dQ=None, dK=None, dV=None, workspace: Optional[torc
     _check([Q, dQ, dK, dV])
     dt = _dt(Q)
     ws, ws_ptr, ws_bytes = _workspace(B, H, n, d, dt, True, Q.device, workspace)
-    with torch.cuda.device(Q.device):
-        stream = torch.cuda.current_stream().cuda_stream
-        rc = getattr(load_library(), _entry)(Q.data_ptr(), K.data_ptr(), V.data_ptr(), _lam(lam, H),
-                                             dO.data_ptr(), dQ.data_ptr(), dK.data_ptr(), dV.data_ptr(),
-                                             B, H, n, d, dt, ws_ptr, ws_bytes, stream)
-    if rc != 0:
-        raise LaError(rc, _entry)
+    _launch(_entry, Q.device, Q.data_ptr(), K.data_ptr(), V.data_ptr(), _lam(lam, H), dO.data_ptr(),
+            dQ.data_ptr(), dK.data_ptr(), dV.data_ptr(), B, H, n, d, dt, ws_ptr, ws_bytes)
     return dQ, dK, dV
 
 
@@ -317,13 +315,8 @@ def la_bwd_saved(Q, K, V, lam, dO, fwd_workspace, dQ=None, dK=None, dV=None,
     dt = _dt(Q)
     ws, ws_ptr, ws_bytes = _workspace(B, H, n, d, dt, False, Q.device, workspace)
     fptr = fwd_workspace.data_ptr() if fwd_workspace is not None else None
-    with torch.cuda.device(Q.device):
-        stream = torch.cuda.current_stream().cuda_stream
-        rc = load_library().la_bwd_saved(Q.data_ptr(), K.data_ptr(), V.data_ptr(), _lam(lam, H), dO.data_ptr(),
-                                         dQ.data_ptr(), dK.data_ptr(), dV.data_ptr(), fptr,
-                                         B, H, n, d, dt, ws_ptr, ws_bytes, stream)
-    if rc != 0:
-        raise LaError(rc, "la_bwd_saved")
+    _launch("la_bwd_saved", Q.device, Q.data_ptr(), K.data_ptr(), V.data_ptr(), _lam(lam, H), dO.data_ptr(),
+            dQ.data_ptr(), dK.data_ptr(), dV.data_ptr(), fptr, B, H, n, d, dt, ws_ptr, ws_bytes)
     return dQ, dK, dV
 
 
@@ -353,13 +346,8 @@ def la_fwd_strided(Q, K, V, lam, O=None, workspace: Optional[torch.Tensor] = Non
     lout = _layout_of([O])
     dt = _dt(Q)
     ws, ws_ptr, ws_bytes = _workspace(B, H, n, d, dt, False, Q.device, workspace)
-    with torch.cuda.device(Q.device):
-        stream = torch.cuda.current_stream().cuda_stream
-        rc = load_library().la_fwd_strided(Q.data_ptr(), K.data_ptr(), V.data_ptr(), _lam(lam, H), O.data_ptr(),
-                                           ctypes.byref(lin), ctypes.byref(lout), B, H, n, d, dt,
-                                           ws_ptr, ws_bytes, stream)
-    if rc != 0:
-        raise LaError(rc, "la_fwd_strided")
+    _launch("la_fwd_strided", Q.device, Q.data_ptr(), K.data_ptr(), V.data_ptr(), _lam(lam, H), O.data_ptr(),
+            ctypes.byref(lin), ctypes.byref(lout), B, H, n, d, dt, ws_ptr, ws_bytes)
     return O
 
 
@@ -375,14 +363,9 @@ def la_bwd_strided(Q, K, V, lam, dO, dQ=None, dK=None, dV=None, workspace: Optio
     lgr = _layout_of([dQ, dK, dV])
     dt = _dt(Q)
     ws, ws_ptr, ws_bytes = _workspace(B, H, n, d, dt, True, Q.device, workspace)
-    with torch.cuda.device(Q.device):
-        stream = torch.cuda.current_stream().cuda_stream
-        rc = load_library().la_bwd_strided(Q.data_ptr(), K.data_ptr(), V.data_ptr(), _lam(lam, H), dO.data_ptr(),
-                                           dQ.data_ptr(), dK.data_ptr(), dV.data_ptr(), ctypes.byref(lin),
-                                           ctypes.byref(ldo), ctypes.byref(lgr), B, H, n, d, dt,
-                                           ws_ptr, ws_bytes, stream)
-    if rc != 0:
-        raise LaError(rc, "la_bwd_strided")
+    _launch("la_bwd_strided", Q.device, Q.data_ptr(), K.data_ptr(), V.data_ptr(), _lam(lam, H), dO.data_ptr(),
+            dQ.data_ptr(), dK.data_ptr(), dV.data_ptr(), ctypes.byref(lin), ctypes.byref(ldo),
+            ctypes.byref(lgr), B, H, n, d, dt, ws_ptr, ws_bytes)
     return dQ, dK, dV
 
 
@@ -398,12 +381,8 @@ def la_fwd_wide(Qw, Kw, V, lam, O=None, workspace: Optional[torch.Tensor] = None
     _check([V, O])
     dt = _dt(V)
     ws, ws_ptr, ws_bytes = _workspace(B, H, n, dv, dt, False, V.device, workspace)
-    with torch.cuda.device(V.device):
-        stream = torch.cuda.current_stream().cuda_stream
-        rc = load_library().la_fwd_wide(Qw.data_ptr(), Kw.data_ptr(), V.data_ptr(), _lam(lam, H), O.data_ptr(),
-                                        B, H, n, dk, dv, dt, ws_ptr, ws_bytes, stream)
-    if rc != 0:
-        raise LaError(rc, "la_fwd_wide")
+    _launch("la_fwd_wide", V.device, Qw.data_ptr(), Kw.data_ptr(), V.data_ptr(), _lam(lam, H), O.data_ptr(), B, H,
+            n, dk, dv, dt, ws_ptr, ws_bytes)
     return O
 
 
@@ -422,13 +401,8 @@ def la_bwd_wide(Qw, Kw, V, lam, dO, dQw=None, dKw=None, dV=None, workspace: Opti
     _check([V, dV])
     dt = _dt(V)
     ws, ws_ptr, ws_bytes = _workspace(B, H, n, dv, dt, True, V.device, workspace)
-    with torch.cuda.device(V.device):
-        stream = torch.cuda.current_stream().cuda_stream
-        rc = load_library().la_bwd_wide(Qw.data_ptr(), Kw.data_ptr(), V.data_ptr(), _lam(lam, H), dO.data_ptr(),
-                                        dQw.data_ptr(), dKw.data_ptr(), dV.data_ptr(),
-                                        B, H, n, dk, dv, dt, ws_ptr, ws_bytes, stream)
-    if rc != 0:
-        raise LaError(rc, "la_bwd_wide")
+    _launch("la_bwd_wide", V.device, Qw.data_ptr(), Kw.data_ptr(), V.data_ptr(), _lam(lam, H), dO.data_ptr(),
+            dQw.data_ptr(), dKw.data_ptr(), dV.data_ptr(), B, H, n, dk, dv, dt, ws_ptr, ws_bytes)
     return dQw, dKw, dV
 
 
@@ -450,11 +424,7 @@ def la_lrpe_rotate_fwd(X, theta, Xw=None):
     if Xw is None:
         Xw = torch.empty((B, H, n, 2 * d), dtype=X.dtype, device=X.device)
     _check([Xw])
-    with torch.cuda.device(X.device):
-        stream = torch.cuda.current_stream().cuda_stream
-        rc = load_library().la_lrpe_rotate_fwd(X.data_ptr(), theta.data_ptr(), Xw.data_ptr(), B, H, n, d, _dt(X), stream)
-    if rc != 0:
-        raise LaError(rc, "la_lrpe_rotate_fwd")
+    _launch("la_lrpe_rotate_fwd", X.device, X.data_ptr(), theta.data_ptr(), Xw.data_ptr(), B, H, n, d, _dt(X))
     return Xw
 
 
@@ -475,14 +445,9 @@ def la_lrpe_rotate_bwd(X, theta, dXw, dX=None, dtheta=None, accumulate: bool = F
     need = la_lrpe_workspace_bytes(B, H, n, d)
     if workspace is None:
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=X.device)
-    with torch.cuda.device(X.device):
-        stream = torch.cuda.current_stream().cuda_stream
-        rc = load_library().la_lrpe_rotate_bwd(X.data_ptr(), theta.data_ptr(), dXw.data_ptr(), dX.data_ptr(),
-                                               dtheta.data_ptr(), 1 if accumulate else 0, workspace.data_ptr(),
-                                               workspace.numel() * workspace.element_size(),
-                                               B, H, n, d, _dt(X), stream)
-    if rc != 0:
-        raise LaError(rc, "la_lrpe_rotate_bwd")
+    _launch("la_lrpe_rotate_bwd", X.device, X.data_ptr(), theta.data_ptr(), dXw.data_ptr(), dX.data_ptr(),
+            dtheta.data_ptr(), 1 if accumulate else 0, workspace.data_ptr(),
+            workspace.numel() * workspace.element_size(), B, H, n, d, _dt(X))
     return dX, dtheta
 
 
@@ -492,12 +457,8 @@ def la_gate_norm_fwd(O, U, eps: float = 0.0, Y=None):
     B, H, n, d = O.shape
     Y = torch.empty_like(O) if Y is None else Y
     _check([O, Y])
-    with torch.cuda.device(O.device):
-        stream = torch.cuda.current_stream().cuda_stream
-        rc = load_library().la_gate_norm_fwd(O.data_ptr(), U.data_ptr(), Y.data_ptr(), float(eps),
-                                             B, H, n, d, _dt(O), stream)
-    if rc != 0:
-        raise LaError(rc, "la_gate_norm_fwd")
+    _launch("la_gate_norm_fwd", O.device, O.data_ptr(), U.data_ptr(), Y.data_ptr(), float(eps), B, H, n, d,
+            _dt(O))
     return Y
 
 
@@ -508,12 +469,8 @@ def la_gate_norm_bwd(O, U, dY, eps: float = 0.0, dO=None, dU=None):
     dO = torch.empty_like(O) if dO is None else dO
     dU = torch.empty_like(O) if dU is None else dU
     _check([O, dO, dU])
-    with torch.cuda.device(O.device):
-        stream = torch.cuda.current_stream().cuda_stream
-        rc = load_library().la_gate_norm_bwd(O.data_ptr(), U.data_ptr(), dY.data_ptr(), dO.data_ptr(),
-                                             dU.data_ptr(), float(eps), B, H, n, d, _dt(O), stream)
-    if rc != 0:
-        raise LaError(rc, "la_gate_norm_bwd")
+    _launch("la_gate_norm_bwd", O.device, O.data_ptr(), U.data_ptr(), dY.data_ptr(), dO.data_ptr(), dU.data_ptr(),
+            float(eps), B, H, n, d, _dt(O))
     return dO, dU
 
 

@@ -161,15 +161,27 @@ int check_lambda(const float *lambda, int H, LaLambdas *out)
         out->lg2[h] = (float)std::log2((double)l);
     }
     for (int h = H; h < LA_MAX_HEADS; ++h) { out->v[h] = 1.0f; out->lg2[h] = 0.0f; }
-    // heads by decreasing lambda (stable): insertion sort, H <= 256
     for (int h = 0; h < LA_MAX_HEADS; ++h) out->order[h] = (uint8_t)h;
-    for (int i = 1; i < H; ++i) {
-        const uint8_t x = out->order[i];
-        int j = i - 1;
-        while (j >= 0 && out->v[out->order[j]] < out->v[x]) { out->order[j + 1] = out->order[j]; --j; }
-        out->order[j + 1] = x;
-    }
     return LA_OK;
+}
+
+// Heads by decreasing lambda (stable, bottom-up merge sort): the order in which a segment-state
+// pre-pass dispatches them.  Only a launch that has a pre-pass needs it (256 heads with rising rates
+// took an insertion sort 20 us).
+void order_heads(LaLambdas *lams, int H)
+{
+    uint8_t tmp[LA_MAX_HEADS];
+    for (int width = 1; width < H; width *= 2) {
+        for (int lo = 0; lo < H; lo += 2 * width) {
+            const int mid = lo + width < H ? lo + width : H, hi = lo + 2 * width < H ? lo + 2 * width : H;
+            int i = lo, j = mid;
+            for (int k = lo; k < hi; ++k) {
+                const bool left = i < mid && (j >= hi || lams->v[lams->order[i]] >= lams->v[lams->order[j]]);
+                tmp[k] = lams->order[left ? i++ : j++];
+            }
+        }
+        std::memcpy(lams->order, tmp, (size_t)H);
+    }
 }
 
 bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
@@ -667,6 +679,7 @@ int forward(const void *Q, const void *K, const void *V, const float *lambda, vo
     const Plan p = make_plan(B, H, n, d, dt);
     rc = check_workspace(p, B, H, d, workspace, workspace_bytes, false);
     if (rc != LA_OK) return rc;
+    if (p.S > 1) order_heads(&lams, H);
     hipStream_t s = (hipStream_t)hip_stream;
     // O = scan(Q, K, V)                                                   (Alg. 5)
     return run_scan<false>(Q, K, V, O, lams, p, B, H, n, d, dt, (float *)workspace, s, kv_in, kv_out, var);
@@ -688,6 +701,7 @@ int backward(const void *Q, const void *K, const void *V, const float *lambda, c
     const Plan p = make_plan(B, H, n, d, dt);
     rc = check_workspace(p, B, H, d, workspace, workspace_bytes, var.fwd_states == nullptr);
     if (rc != LA_OK) return rc;
+    if (p.S > 1) order_heads(&lams, H);
     return run_backward(Q, K, V, dO, dQ, dK, dV, lams, p, B, H, n, d, dt, (float *)workspace,
                         (hipStream_t)hip_stream, var);
 }
