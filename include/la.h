@@ -329,7 +329,10 @@ const char *la_strerror(int status);
 /*
  * Plan introspection (host arithmetic only): the tile length (the paper's
  * "block size B"), the segment length in tokens and the number of segments per
- * (batch, head) scan that la_fwd / la_bwd will use for this problem.  Any
+ * (batch, head) scan that la_fwd / la_bwd will use for this problem, i.e. the
+ * segments whose states the scratch holds.  (Small problems may run in shorter
+ * pieces whose workgroups rebuild their entering states and leave the scratch
+ * unread; la_fwd writes the segment states all the same.)  Any
  * output pointer may be NULL.  Returns an la_status.
  */
 int la_plan(int B, int H, int n, int d, la_dtype dt,

@@ -58,6 +58,7 @@ struct Switches {
     std::atomic<long> staged_prepass{0}; // != 0: bf16 runs the register-staged segment-state pre-pass
     std::atomic<long> prepass_groups{0}; // 1, 2: wave groups per workgroup of the direct-to-LDS pre-pass (own choice: 4)
     std::atomic<long> no_trio{0};        // != 0: la_bwd's direct-to-LDS block scans as a dQ launch and a paired dK / dV launch
+    std::atomic<long> piece{0};          // > 0: piece length of block scans that rebuild their entering states; < 0: none
     std::atomic<long> wide_slices{0};    // != 0: la_fwd_wide always runs accumulated scans over d_v-wide slices
     std::atomic<long> ablate{0};         // 1..4: measurement-only variants of the direct-to-LDS scan
     std::atomic<long> staged_scan{0};    // != 0: bf16 runs the register-staged block scan
@@ -73,6 +74,7 @@ std::atomic<long> *find_switch(const char *name)
     if (!std::strcmp(name, "f32_plain")) return &g_sw.f32_plain;
     if (!std::strcmp(name, "staged_scan")) return &g_sw.staged_scan;
     if (!std::strcmp(name, "ablate")) return &g_sw.ablate;
+    if (!std::strcmp(name, "piece")) return &g_sw.piece;
     if (!std::strcmp(name, "wide_slices")) return &g_sw.wide_slices;
     if (!std::strcmp(name, "no_trio")) return &g_sw.no_trio;
     if (!std::strcmp(name, "staged_prepass")) return &g_sw.staged_prepass;
@@ -292,6 +294,30 @@ hipError_t launch_bf16_dma(const ScanLaunch &a, const LaLambdas &lams, hipStream
               : launch_bf16_dma_variant<REV, false, 0>(a, lams, s);
 }
 
+// The dynamic LDS size of every kernel that a plain bf16 forward or backward call may choose between, set
+// together at the first such call: which of them runs depends on the decay rates too, and a call that is
+// being captured into a graph should only launch.
+template <int D>
+hipError_t prepare_bf16()
+{
+    static std::once_flag once;
+    static hipError_t err = hipSuccess;
+    std::call_once(once, [&] {
+        const size_t scan = DmaCfg<3, D>::lds_bytes, pre = DmaPrepassCfg<4, D>::lds_bytes;
+        const hipError_t all[] = {
+            allow_lds(la_scan_bf16_dma<false, true, 0, 3, false, false, D>, scan),
+            allow_lds(la_scan_bf16_dma<false, true, 0, 3, false, true, D>, scan),
+            allow_lds(la_scan_bf16_dma<false, true, 0, 3, true, false, D>, scan),
+            allow_lds(la_scan_bf16_dma<false, true, 0, 3, true, true, D>, scan),
+            allow_lds(la_scan_bf16_dma<false, true, 0, 3, false, true, D, true>, scan),
+            allow_lds(la_scan_bf16_dma<false, true, 0, 3, true, true, D, true>, scan),
+            allow_lds(la_prepass_bf16_dma<4, false, D>, pre), allow_lds(la_prepass_bf16_dma<4, true, D>, pre)};
+        for (const hipError_t e : all)
+            if (e != hipSuccess) err = e;
+    });
+    return err;
+}
+
 template <int G, bool STRIDED = false, int D = 128>
 hipError_t launch_prepass_bf16_dma(const ScanLaunch &a, const LaLambdas &lams, hipStream_t s)
 {
@@ -347,6 +373,18 @@ hipError_t launch_f32s(const ScanLaunch &a, const LaLambdas &lams, hipStream_t s
     const unsigned n = (unsigned)a.nroles, items = (unsigned)a.items;
     dim3 grid(STATE_ONLY || n == 1 ? n * items : n * ((items + 7) / 8 * 8)), block(Cfg::NT);
     hipLaunchKernelGGL(kern, grid, block, Cfg::lds_bytes(STATE_ONLY), s, a, lams);
+    return hipGetLastError();
+}
+
+// Block scans that rebuild their entering states: la_fwd's (one role) and la_bwd's (three).
+template <bool TRIO, int D>
+hipError_t launch_bf16_rebuild(const ScanLaunch &a, const LaLambdas &lams, hipStream_t s)
+{
+    using Cfg = DmaCfg<3, D>;
+    auto kern = la_scan_bf16_dma<false, true, 0, 3, TRIO, true, D, true>;   // attributes: prepare_bf16
+    const unsigned items = (unsigned)a.items;
+    dim3 grid(TRIO ? 3u * ((items + 7) / 8 * 8) : items), block(Cfg::NT);
+    hipLaunchKernelGGL(kern, grid, block, Cfg::lds_bytes, s, a, lams);
     return hipGetLastError();
 }
 
@@ -441,7 +479,61 @@ ScanArgs make_args(const void *A, const void *Bm, const void *C, void *Out, cons
     a.st_out = nullptr;
     a.act = 0;
     a.E = nullptr;
+    a.saved = nullptr; a.saved_L = 1; a.saved_S = 0;
     return a;
+}
+
+// Length of the pieces into which a launch of `roles` block scans is cut when its workgroups rebuild
+// their entering states themselves (la_scan_bf16_dma's REBUILD); 0: the plan's segments, with their
+// pre-pass if any.
+// A launch that leaves most of the chip idle is bound by its longest chain of blocks.  Times in us,
+// fitted to graph replays of la_fwd and la_bwd on 1 .. 128 scans of 64 .. 4096 tokens (d = 128 / 64):
+//   a launch 5.0 / 4.2 (first loads, states, drain); a block that only updates the state 0.77 / 0.64; a
+//   block of a piece 1.2 / 0.87; a block of the plain scan 1.1 / 0.75; pre-pass and segment scan
+//   14 / 9 and what their states take, 0.07 / 0.03 per segment (twice that in la_bwd);
+//   two workgroups to a compute unit (four of d = 64) 1.3 times the time, beyond that by the number.
+// So the rule weighs the plan's chain against launch + leading blocks + own blocks of every piece length
+// and takes the best if the estimate is a tenth better.  Measured, la_fwd / la_bwd in us, plan -> rule:
+//   d = 128:  8 scans of 512 tokens  22.6 / 22.9 -> 16.8 / 17.1     16 of 1000  40.9 / 43.2 -> 29.4 / 32.9
+//             12 of 675              39.5 / 41.2 -> 21.3 / 23.1     5 of 1869, lambda = 0.9  35.1 / 38.0 -> 13.9 / 16.3
+//   d = 64:   11 of 597              25.0 / 26.8 -> 15.8 / 18.2     16 of 1215, lambda = 0.95  26.1 / 26.3 -> 18.1 / 20.7
+// (lambda = 1 or up to 0.9999 where none is given); on 70 shapes of 1 .. 200 scans it never lost more than 2 %.
+// Six LDS stages instead of three made the same launches 30 % slower.
+int rebuild_piece(const Plan &p, long scans, int H, int n, int d, la_dtype dt, int roles, const LaLambdas &lams,
+                  float skip_bits)
+{
+    const auto on = [](const std::atomic<long> &x) { return x.load(std::memory_order_relaxed) != 0; };
+    const long forced = g_sw.piece.load(std::memory_order_relaxed);
+    if (dt != LA_BF16 || forced < 0 || on(g_sw.lseg) || on(g_sw.staged_scan) || on(g_sw.staged_prepass) ||
+        on(g_sw.no_trio) || on(g_sw.no_pair) || on(g_sw.ablate) || on(g_sw.store_policy))
+        return 0;
+    if (forced > 0) return round_up((int)(forced < p.L ? forced : p.L), 32);
+
+    const bool wide = d == 128;
+    const double launch = wide ? 5.0 : 4.2, lead = wide ? 0.77 : 0.64, own = wide ? 1.2 : 0.87, plain = wide ? 1.1 : 0.75;
+    const int unit = wide ? kComputeUnits : 2 * kComputeUnits;   // workgroups that run undisturbed
+    const auto load = [&](double wgs) { return wgs <= unit ? 1.0 : wgs <= 2 * unit ? 1.3 : 0.65 * wgs / unit; };
+    if ((double)roles * scans * p.S > 3.0 * unit) return 0;      // the chip is full: bound by bytes, not by the chain
+
+    double reach = 0.0;                                          // rows a leading chain may need, at most
+    for (int h = 0; h < H; ++h) {
+        const double r = lams.lg2[h] < 0.0f && skip_bits > 0.0f ? skip_bits / -(double)lams.lg2[h] : 1e30;
+        if (r > reach) reach = r;
+    }
+    const double segs = (double)scans * p.S;
+    double best = launch + load(roles * segs) * (p.S > 1 ? p.L : n) / 32.0 * plain;
+    if (p.S > 1) best += (wide ? 14.0 + 1.25 * (p.L - 512) / 128 : 9.0) + (wide ? 0.07 : 0.03) * segs * (roles > 1 ? 2 : 1);
+    best *= 0.9;
+    int piece = 0;
+    for (int len = 64; len <= p.L; len *= 2) {
+        const double wgs = (double)roles * scans * ((n + len - 1) / len);
+        // (la_bwd_saved wants la_fwd's states at multiples of the plan's segments)
+        if (wgs > 3.0 * unit || (p.S > 1 && p.L % len != 0)) continue;
+        const double before = n - len < reach + 64 ? (n > len ? n - len : 0) : reach + 64;
+        const double t = launch + load(wgs) * (before / 32 * lead + (len < n ? len : n) / 32.0 * own);
+        if (t < best) { best = t; piece = len; }
+    }
+    return piece;
 }
 
 // Segment-state pre-pass: the local end state of every segment of scan(., Bm, C),
@@ -514,6 +606,19 @@ int run_scan(const void *A, const void *Bm, const void *C, void *Out, const LaLa
     a.rev = REV ? 1 : 0;
     a.st_in = st_in;
     a.st_out = st_out;
+    const bool plain = a.act == 0 || a.act == LA_ACT_EXT;
+    if (dt == LA_BF16 && (d == 64 ? prepare_bf16<64>() : prepare_bf16<128>()) != hipSuccess) return LA_ERR_LAUNCH;
+    const int piece = !REV && plain ? rebuild_piece(p, scans, H, n, d, dt, 1, lams, a.skip_bits) : 0;
+    if (piece > 0) {
+        if (p.S > 1) { a.saved = a.states; a.saved_L = p.L; a.saved_S = p.S; }    // for la_bwd_saved
+        a.states = nullptr;
+        a.L = piece; a.S = (n + piece - 1) / piece;
+        ScanLaunch l = {};
+        l.r[0] = a; l.nroles = 1; l.items = (int)(scans * a.S);
+        ScopedTimer t(s);
+        const hipError_t e = d == 64 ? launch_bf16_rebuild<false, 64>(l, lams, s) : launch_bf16_rebuild<false, 128>(l, lams, s);
+        return e == hipSuccess ? LA_OK : LA_ERR_LAUNCH;
+    }
     if (p.S > 1) {
         int rc = run_prepass(&a, 1, lams, scans, d, dt, s);
         if (rc == LA_OK) rc = run_segment_scan<REV>(a, lams, scans, d, s);
@@ -588,6 +693,19 @@ int run_backward(const void *Q, const void *K, const void *V, const void *dO, vo
         av.lA = av.lB = *var.in; av.lC = *var.dout; av.lO = *var.out;                   // (K, Q, dO) -> dV
         pre[0].act |= LA_ACT_EXT; pre[1].act |= LA_ACT_EXT; av.act |= LA_ACT_EXT;
     }
+    const int acts = pre[0].act | pre[1].act | av.act;
+    const bool all_ext = pre[0].act == LA_ACT_EXT && pre[1].act == LA_ACT_EXT && av.act == LA_ACT_EXT;
+    if (dt == LA_BF16 && (d == 64 ? prepare_bf16<64>() : prepare_bf16<128>()) != hipSuccess) return LA_ERR_LAUNCH;
+    const int piece = !reuse && (acts == 0 || all_ext) ? rebuild_piece(p, scans, H, n, d, dt, 3, lams, av.skip_bits) : 0;
+    if (piece > 0) {
+        ScanLaunch l;
+        l.r[0] = pre[0]; l.r[1] = pre[1]; l.r[2] = av; l.nroles = 3;
+        for (ScanArgs &r : l.r) { r.states = nullptr; r.L = piece; r.S = (n + piece - 1) / piece; }
+        l.items = (int)(scans * l.r[0].S);
+        ScopedTimer t(s);
+        const hipError_t e = d == 64 ? launch_bf16_rebuild<true, 64>(l, lams, s) : launch_bf16_rebuild<true, 128>(l, lams, s);
+        return e == hipSuccess ? LA_OK : LA_ERR_LAUNCH;
+    }
     if (p.S > 1) {
         int rc;
         if (reuse) {
@@ -599,8 +717,6 @@ int run_backward(const void *Q, const void *K, const void *V, const void *dO, vo
         }
         if (rc != LA_OK) return rc;
     }
-    const int acts = pre[0].act | pre[1].act | av.act;
-    const bool all_ext = pre[0].act == LA_ACT_EXT && pre[1].act == LA_ACT_EXT && av.act == LA_ACT_EXT;
     const bool one_launch = !g_sw.no_trio.load(std::memory_order_relaxed) && !g_sw.no_pair.load(std::memory_order_relaxed) &&
         (dt == LA_BF16 ? (acts == 0 || all_ext) && !g_sw.staged_scan.load(std::memory_order_relaxed) &&
                              !g_sw.ablate.load(std::memory_order_relaxed)

@@ -11,6 +11,8 @@
  *                    of the planner's choice
  *   "no_pair"        != 0: the dK and dV scans of the backward pass run as two launches
  *                    instead of one XCD-paired launch
+ *   "piece"          > 0: bf16 block scans of la_fwd / la_bwd run in pieces of that many tokens (rounded up to
+ *                    32) whose workgroups rebuild their entering states, without a pre-pass; < 0: never
  *   "no_decay_skip"  != 0: the segment-state pre-pass reads every block, also those whose
  *                    decay weight is below its cut-off
  *   "f32_plain"      != 0: fp32 runs the plain FMA kernel instead of the matrix-core one

@@ -150,7 +150,14 @@ __device__ __forceinline__ U2 lds_read_tr(const unsigned char *p)
 // fit the Infinity Cache (sequences or segments of up to about 1024 tokens), a part of the reads
 // that the forward and the reversed roles have in common.
 // STRIDED: every operand has its own layout (ScanArgs::lA .. lO) instead of contiguous slabs.
-template <bool REV_, bool NT_STORE, int ABL, int NS_, bool TRIO = false, bool STRIDED = false, int D_ = 128>
+// REBUILD: short pieces of a scan for launches that would leave most of the chip idle.  A workgroup
+//   makes its entering state itself: before its own blocks it walks those that precede them in scan
+//   order (as far back as the decay cut-off reaches) with the state update alone, no A tile, no result,
+//   so that no pre-pass and no segment scan run first and pieces may be shorter than what segment
+//   states in scratch would allow.  ScanArgs::L is the piece, S the pieces per scan, `states` unused;
+//   `saved` (if any) receives the states at multiples of saved_L, as the segment scan leaves them.
+template <bool REV_, bool NT_STORE, int ABL, int NS_, bool TRIO = false, bool STRIDED = false, int D_ = 128,
+          bool REBUILD = false>
 __global__ __launch_bounds__(2 * D_, NS_ <= 3 ? 2 : 1) void la_scan_bf16_dma(ScanLaunch launch, LaLambdas lams)
 {
     using Cfg = DmaCfg<NS_, D_>;
@@ -195,8 +202,23 @@ __global__ __launch_bounds__(2 * D_, NS_ <= 3 ? 2 : 1) void la_scan_bf16_dma(Sca
     const float lg = lams.lg2[scan % a.H];
     auto pw = [lg](int k) -> float { return exp2f((float)k * lg); };
 
-    const int seg_lo = seg * a.L;
-    const int seg_hi = min(a.n, seg_lo + a.L);
+    int seg_lo = seg * a.L;
+    int seg_hi = min(a.n, seg_lo + a.L);
+    int nwarm = 0;                             // REBUILD: leading blocks that only update the state
+    bool from_start = true;                    // ... and whether they begin where the scan does
+    if (REBUILD) {
+        // rows before the piece (in scan order) whose weight in the entering state is not negligible
+        const int before = REV ? a.n - seg_hi : seg_lo;
+        int rows = before;
+        if (a.skip_bits > 0.f && lg < 0.f) {
+            const float reach = a.skip_bits / -lg;
+            if (reach < (float)before) rows = min(before, ((int)(reach / BK) + 2) * BK);
+        }
+        from_start = rows == before;
+        nwarm = (rows + BK - 1) / BK;
+        if (REV) seg_hi += rows;
+        else seg_lo -= rows;
+    }
     const int nblk = (seg_hi - seg_lo + BK - 1) / BK;
 
     // tiles of a stage, in LDS order: A, Bm, C.  STRIDED: every operand has its own layout (slab
@@ -257,9 +279,10 @@ __global__ __launch_bounds__(2 * D_, NS_ <= 3 ? 2 : 1) void la_scan_bf16_dma(Sca
 
     // ---- running state: St[i][j], j in this wave's slice ------------------------------
     f32x16_t st[MT_D];
-    const float *gSt = la_entering_state(a, scan, seg, REV, lg, D * D);
+    const float *gSt = REBUILD ? (!REV && from_start && a.st_in ? a.st_in + (size_t)scan * (D * D) : nullptr)
+                               : la_entering_state(a, scan, seg, REV, lg, D * D);
     const bool has_init = gSt != nullptr;
-    if (has_init && a.transpose_init) {
+    if (!REBUILD && has_init && a.transpose_init) {
         // the stored state is that of the scan with Bm and C exchanged: through LDS, transposed
         float *sT = reinterpret_cast<float *>(smem_dma);         // [D][D+1]
         for (int e = tid * 4; e < D * D; e += 4 * Cfg::NT) {
@@ -276,14 +299,17 @@ __global__ __launch_bounds__(2 * D_, NS_ <= 3 ? 2 : 1) void la_scan_bf16_dma(Sca
                 st[mt][v] = sT[(32 * w + l32) * (D + 1) + i];
             }
         __syncthreads();
+    } else if (has_init) {                      // (a condition per element would be a branch per load)
+        const float *p = gSt + 4 * g * D + 32 * w + l32;
+#pragma unroll
+        for (int mt = 0; mt < MT_D; ++mt)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) st[mt][v] = p[(32 * mt + 8 * (v >> 2) + (v & 3)) * D];
     } else {
 #pragma unroll
         for (int mt = 0; mt < MT_D; ++mt)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int i = 32 * mt + 8 * (v >> 2) + 4 * g + (v & 3);
-                st[mt][v] = has_init ? gSt[(size_t)i * D + 32 * w + l32] : 0.0f;
-            }
+            for (int v = 0; v < 16; ++v) st[mt][v] = 0.0f;
     }
 
     // ---- global -> LDS loads of one block ------------------------------------------------
@@ -291,7 +317,7 @@ __global__ __launch_bounds__(2 * D_, NS_ <= 3 ? 2 : 1) void la_scan_bf16_dma(Sca
     // zeroed in LDS by the lane that fetched them once the load has landed.
     // Tiles that no other workgroup reads carry the non-temporal hint: everything in a
     // single-scan launch, the A operand in a paired launch.
-    const bool nt_all = launch.nroles == 1;
+    const bool nt_all = launch.nroles == 1 && !REBUILD;
     const bool nt_a = !TRIO;                    // the A operand is private to a scan except in a trio
     const auto blk_of = [&](int ib) { return REV ? (nblk - 1 - ib) : ib; };
     auto issue = [&](int ib, int stage) {
@@ -301,7 +327,8 @@ __global__ __launch_bounds__(2 * D_, NS_ <= 3 ? 2 : 1) void la_scan_bf16_dma(Sca
         for (int j = 0; j < SPW; ++j) {
             const size_t row = (size_t)min(t0 + dma_row[j], seg_hi - 1);
             const uint32_t dst = lds0 + stage * Cfg::STAGE_BYTES + (SPW * w + j) * 1024;   // lane l lands at + 16 l
-            if (nt_a) dma_load16<true>(gT[0] + row * ldT[0] + dma_col[j], dst);
+            if (REBUILD && ib < nwarm) {}      // no A tile
+            else if (nt_a) dma_load16<true>(gT[0] + row * ldT[0] + dma_col[j], dst);
             else dma_load16<false>(gT[0] + row * ldT[0] + dma_col[j], dst);
             if (nt_all) {
 #pragma unroll
@@ -330,6 +357,21 @@ __global__ __launch_bounds__(2 * D_, NS_ <= 3 ? 2 : 1) void la_scan_bf16_dma(Sca
         }
     };
 
+    // REBUILD: the state entering a multiple of saved_L, to the slot where la_entering_state looks for it
+    const int own_lo = seg_lo + (REBUILD && !REV ? nwarm * BK : 0);
+    const bool seg_state_due = REBUILD && !REV && a.saved != nullptr && own_lo % a.saved_L == 0;
+    auto save_state = [&]() {
+        const int s0 = own_lo / a.saved_L;
+        const bool chain_free = a.skip_bits > 0.f && -lg * (float)a.saved_L >= a.skip_bits;
+        if (chain_free && s0 == 0) return;
+        float *p = a.saved + ((size_t)scan * a.saved_S + (chain_free ? s0 - 1 : s0)) * (size_t)(D * D) +
+                   4 * g * D + 32 * w + l32;
+#pragma unroll
+        for (int mt = 0; mt < MT_D; ++mt)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) p[(32 * mt + 8 * (v >> 2) + (v & 3)) * D] = st[mt][v];
+    };
+
     constexpr int PF = NS - 1;                 // blocks of prefetch
 #pragma unroll
     for (int i = 0; i < PF; ++i)
@@ -346,7 +388,11 @@ __global__ __launch_bounds__(2 * D_, NS_ <= 3 ? 2 : 1) void la_scan_bf16_dma(Sca
         // blocks ib + 1 .. ib + PF - 1, as far as they exist (at the start the first PF blocks
         // were issued back to back, with fewer stores among them; near the end some loads were
         // never issued).  Short segments simply wait for everything.
-        if (nblk < 2 * PF + 1 || ib + 1 >= nblk) {
+        const bool warm = REBUILD && ib < nwarm;
+        if (REBUILD) {                          // a leading block loads two tiles and stores nothing
+            const int young = min(PF - 1, nblk - 1 - ib), lead = max(0, min(young, nwarm - 1 - ib));
+            la_wait_vm_le<(PF - 1) * (LOADS + ST)>(LOADS * young - SPW * lead + ST * min(PF - 1, max(0, ib - nwarm)));
+        } else if (nblk < 2 * PF + 1 || ib + 1 >= nblk) {
             la_wait_vm<0>();
         } else {
             const int young = min(PF - 1, nblk - 1 - ib);    // blocks whose loads are younger
@@ -386,37 +432,39 @@ __global__ __launch_bounds__(2 * D_, NS_ <= 3 ? 2 : 1) void la_scan_bf16_dma(Sca
         }
         const unsigned char *sA = sb, *sB = sb + Cfg::TILE_BYTES, *sC = sb + 2 * Cfg::TILE_BYTES;
 
-        // ---- row fragments of A (both products) and of Bm (scores) ---------------------
-        U4 fa[KS_D];
+        if (REBUILD && seg_state_due && ib == nwarm) save_state();
+        f32x16_t s = {0}, x = {0};
+        if (!warm) {
+            // ---- row fragments of A (both products) and of Bm (scores) ---------------------
+            U4 fa[KS_D];
 #pragma unroll
-        for (int ks = 0; ks < KS_D; ++ks) fa[ks] = *(const U4 *)(sA + ro_base + (((2 * ks) ^ ro_sw) << 4));
-        // ---- scores: S^T = Bm A^T (lane = q, registers = keys), in two halves of the k range
-        f32x16_t s = {0};
+            for (int ks = 0; ks < KS_D; ++ks) fa[ks] = *(const U4 *)(sA + ro_base + (((2 * ks) ^ ro_sw) << 4));
+            // ---- scores: S^T = Bm A^T (lane = q, registers = keys), in two halves of the k range
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            U4 fb[KS_D / 2];
+            for (int h = 0; h < 2; ++h) {
+                U4 fb[KS_D / 2];
 #pragma unroll
-            for (int k = 0; k < KS_D / 2; ++k)
-                fb[k] = *(const U4 *)(sB + ro_base + (((2 * (KS_D / 2 * h + k)) ^ ro_sw) << 4));
-            LA_BATCH_FENCE();
+                for (int k = 0; k < KS_D / 2; ++k)
+                    fb[k] = *(const U4 *)(sB + ro_base + (((2 * (KS_D / 2 * h + k)) ^ ro_sw) << 4));
+                LA_BATCH_FENCE();
 #pragma unroll
-            for (int k = 0; k < KS_D / 2; ++k) s = mfma32(fb[k], fa[KS_D / 2 * h + k], s);
-        }
-        // ---- inter block: x^T = St^T A^T; the state operand is made from the accumulators:
-        // lane half g holds rows 4g..4g+3 and 8+4g..8+4g+3 of every 16, the operand wants
-        // rows 8g..8g+7: the halves exchange what they lack.
-        f32x16_t x = {0};
+                for (int k = 0; k < KS_D / 2; ++k) s = mfma32(fb[k], fa[KS_D / 2 * h + k], s);
+            }
+            // ---- inter block: x^T = St^T A^T; the state operand is made from the accumulators:
+            // lane half g holds rows 4g..4g+3 and 8+4g..8+4g+3 of every 16, the operand wants
+            // rows 8g..8g+7: the halves exchange what they lack.
 #pragma unroll
-        for (int ks = 0; ks < KS_D; ++ks) {
-            const int mt = ks >> 1, h8 = 8 * (ks & 1);
-            const uint32_t x0 = pack2_bf16(st[mt][h8 + 0], st[mt][h8 + 1]);
-            const uint32_t x1 = pack2_bf16(st[mt][h8 + 2], st[mt][h8 + 3]);
-            const uint32_t y0 = pack2_bf16(st[mt][h8 + 4], st[mt][h8 + 5]);
-            const uint32_t y1 = pack2_bf16(st[mt][h8 + 6], st[mt][h8 + 7]);
-            const auto s0 = __builtin_amdgcn_permlane32_swap(x0, y0, false, false);
-            const auto s1 = __builtin_amdgcn_permlane32_swap(x1, y1, false, false);
-            const U4 so = {s0[0], s1[0], s0[1], s1[1]};
-            x = mfma32(so, fa[ks], x);
+            for (int ks = 0; ks < KS_D; ++ks) {
+                const int mt = ks >> 1, h8 = 8 * (ks & 1);
+                const uint32_t x0 = pack2_bf16(st[mt][h8 + 0], st[mt][h8 + 1]);
+                const uint32_t x1 = pack2_bf16(st[mt][h8 + 2], st[mt][h8 + 3]);
+                const uint32_t y0 = pack2_bf16(st[mt][h8 + 4], st[mt][h8 + 5]);
+                const uint32_t y1 = pack2_bf16(st[mt][h8 + 6], st[mt][h8 + 7]);
+                const auto s0 = __builtin_amdgcn_permlane32_swap(x0, y0, false, false);
+                const auto s1 = __builtin_amdgcn_permlane32_swap(x1, y1, false, false);
+                const U4 so = {s0[0], s1[0], s0[1], s1[1]};
+                x = mfma32(so, fa[ks], x);
+            }
         }
         // ---- C^T fragments of this wave's slice (transposing reads), plain and weighted ---
         U4 cf[KS_B], cw[KS_B];
@@ -427,26 +475,28 @@ __global__ __launch_bounds__(2 * D_, NS_ <= 3 ? 2 : 1) void la_scan_bf16_dma(Sca
             const U2 hi = lds_read_tr(p + 8 * PITCH + ((((4 * w) ^ tr_sw ^ SW8)) << 4));
             cf[ks] = U4{lo[0], lo[1], hi[0], hi[1]};
         }
-        // ---- P = bf16(S * mask) stays in registers: it is already the operand of the intra product
-        U4 pk[KS_B];
+        if (!warm) {
+            // ---- P = bf16(S * mask) stays in registers: it is already the operand of the intra product
+            U4 pk[KS_B];
 #pragma unroll
-        for (int ks = 0; ks < KS_B; ++ks)
+            for (int ks = 0; ks < KS_B; ++ks)
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                pk[ks][e] = pack2_bf16(s[8 * ks + 2 * e] * mk[8 * ks + 2 * e],
-                                       s[8 * ks + 2 * e + 1] * mk[8 * ks + 2 * e + 1]);
+                for (int e = 0; e < 4; ++e)
+                    pk[ks][e] = pack2_bf16(s[8 * ks + 2 * e] * mk[8 * ks + 2 * e],
+                                           s[8 * ks + 2 * e + 1] * mk[8 * ks + 2 * e + 1]);
 #pragma unroll
-        for (int v = 0; v < 16; ++v) x[v] *= rsq;
-        // ---- intra block: Out^T += C^T P^T
+            for (int v = 0; v < 16; ++v) x[v] *= rsq;
+            // ---- intra block: Out^T += C^T P^T
 #pragma unroll
-        for (int ks = 0; ks < KS_B; ++ks) x = mfma32(cf[ks], pk[ks], x);
-        // ---- Out tile -> LDS (bf16): lane holds 4 consecutive features per v4
+            for (int ks = 0; ks < KS_B; ++ks) x = mfma32(cf[ks], pk[ks], x);
+            // ---- Out tile -> LDS (bf16): lane holds 4 consecutive features per v4
 #pragma unroll
-        for (int v4 = 0; v4 < 4; ++v4) {
-            U2 o;
-            o[0] = pack2_bf16(x[4 * v4 + 0], x[4 * v4 + 1]);
-            o[1] = pack2_bf16(x[4 * v4 + 2], x[4 * v4 + 3]);
-            *(U2 *)(sO + l32 * PITCH + (((4 * w + v4) ^ (l32 & (CPR - 1))) << 4) + 8 * g) = o;
+            for (int v4 = 0; v4 < 4; ++v4) {
+                U2 o;
+                o[0] = pack2_bf16(x[4 * v4 + 0], x[4 * v4 + 1]);
+                o[1] = pack2_bf16(x[4 * v4 + 2], x[4 * v4 + 3]);
+                *(U2 *)(sO + l32 * PITCH + (((4 * w + v4) ^ (l32 & (CPR - 1))) << 4) + 8 * g) = o;
+            }
         }
 #pragma unroll
         for (int ks = 0; ks < KS_B; ++ks)
@@ -473,8 +523,10 @@ __global__ __launch_bounds__(2 * D_, NS_ <= 3 ? 2 : 1) void la_scan_bf16_dma(Sca
             for (int ks = 0; ks < KS_B; ++ks) u = mfma32(bt[ks], cw[ks], u);
             st[mt] = u;
         }
-        LA_LDS_BARRIER();                       // the Out tile is complete
-        store_out(t0);
+        if (!warm) {
+            LA_LDS_BARRIER();                   // the Out tile is complete
+            store_out(t0);
+        }
         stage = stage + 1 < NS ? stage + 1 : 0;
     }
     if (ABL != 0) {                             // keep the arithmetic alive: one store per wave
