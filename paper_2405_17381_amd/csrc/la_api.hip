@@ -294,7 +294,7 @@ hipError_t launch_bf16_dma(const ScanLaunch &a, const LaLambdas &lams, hipStream
               : launch_bf16_dma_variant<REV, false, 0>(a, lams, s);
 }
 
-// The dynamic LDS size of every kernel that a plain bf16 forward or backward call may choose between, set
+// The dynamic LDS size of every kernel that a plain forward or backward call may choose between, set
 // together at the first such call: which of them runs depends on the decay rates too, and a call that is
 // being captured into a graph should only launch.
 template <int D>
@@ -360,15 +360,32 @@ hipError_t launch_f32(const ScanLaunch &a, const LaLambdas &lams, hipStream_t s)
     return hipGetLastError();
 }
 
+template <int D>
+hipError_t prepare_f32()
+{
+    static std::once_flag once;
+    static hipError_t err = hipSuccess;
+    std::call_once(once, [&] {
+        const hipError_t all[] = {allow_lds(la_scan_f32s<D, false>, F32sCfg<D>::lds_bytes(false)),
+                                  allow_lds(la_scan_f32s<D, true>, F32sCfg<D>::lds_bytes(true)),
+                                  allow_lds(la_scan_f32s<D, false, true>, F32sCfg<D>::lds_bytes(false))};
+        for (const hipError_t e : all)
+            if (e != hipSuccess) err = e;
+    });
+    return err;
+}
+
+hipError_t prepare(int d, la_dtype dt)
+{
+    if (dt == LA_F32) return d == 64 ? prepare_f32<64>() : prepare_f32<128>();
+    return d == 64 ? prepare_bf16<64>() : prepare_bf16<128>();
+}
+
 template <int D, bool STATE_ONLY>
 hipError_t launch_f32s(const ScanLaunch &a, const LaLambdas &lams, hipStream_t s)
 {
     using Cfg = F32sCfg<D>;
-    auto kern = la_scan_f32s<D, STATE_ONLY>;
-    static std::once_flag once;
-    static hipError_t attr_err = hipSuccess;
-    std::call_once(once, [&] { attr_err = allow_lds(kern, Cfg::lds_bytes(STATE_ONLY)); });
-    if (attr_err != hipSuccess) return attr_err;
+    auto kern = la_scan_f32s<D, STATE_ONLY>;                 // attributes: prepare_f32
     // several block scans in one launch: items padded to a multiple of the 8 XCDs
     const unsigned n = (unsigned)a.nroles, items = (unsigned)a.items;
     dim3 grid(STATE_ONLY || n == 1 ? n * items : n * ((items + 7) / 8 * 8)), block(Cfg::NT);
@@ -386,6 +403,25 @@ hipError_t launch_bf16_rebuild(const ScanLaunch &a, const LaLambdas &lams, hipSt
     dim3 grid(TRIO ? 3u * ((items + 7) / 8 * 8) : items), block(Cfg::NT);
     hipLaunchKernelGGL(kern, grid, block, Cfg::lds_bytes, s, a, lams);
     return hipGetLastError();
+}
+
+// ... and in fp32.
+template <int D>
+hipError_t launch_f32_rebuild(const ScanLaunch &a, const LaLambdas &lams, hipStream_t s)
+{
+    using Cfg = F32sCfg<D>;
+    auto kern = la_scan_f32s<D, false, true>;                // attributes: prepare_f32
+    const unsigned n = (unsigned)a.nroles, items = (unsigned)a.items;
+    dim3 grid(n == 1 ? items : n * ((items + 7) / 8 * 8)), block(Cfg::NT);
+    hipLaunchKernelGGL(kern, grid, block, Cfg::lds_bytes(false), s, a, lams);
+    return hipGetLastError();
+}
+
+hipError_t launch_rebuild(const ScanLaunch &a, const LaLambdas &lams, int d, la_dtype dt, hipStream_t s)
+{
+    if (dt == LA_F32) return d == 64 ? launch_f32_rebuild<64>(a, lams, s) : launch_f32_rebuild<128>(a, lams, s);
+    if (a.nroles == 3) return d == 64 ? launch_bf16_rebuild<true, 64>(a, lams, s) : launch_bf16_rebuild<true, 128>(a, lams, s);
+    return d == 64 ? launch_bf16_rebuild<false, 64>(a, lams, s) : launch_bf16_rebuild<false, 128>(a, lams, s);
 }
 
 // bf16, direct-to-LDS family: plain launches and launches whose operands have their own layouts
@@ -486,17 +522,27 @@ ScanArgs make_args(const void *A, const void *Bm, const void *C, void *Out, cons
 // Length of the pieces into which a launch of `roles` block scans is cut when its workgroups rebuild
 // their entering states themselves (la_scan_bf16_dma's REBUILD); 0: the plan's segments, with their
 // pre-pass if any.
-// A launch that leaves most of the chip idle is bound by its longest chain of blocks.  Times in us,
-// fitted to graph replays of la_fwd and la_bwd on 1 .. 128 scans of 64 .. 4096 tokens (d = 128 / 64):
-//   a launch 5.0 / 4.2 (first loads, states, drain); a block that only updates the state 0.77 / 0.64; a
-//   block of a piece 1.2 / 0.87; a block of the plain scan 1.1 / 0.75; pre-pass and segment scan
-//   14 / 9 and what their states take, 0.07 / 0.03 per segment (twice that in la_bwd);
-//   two workgroups to a compute unit (four of d = 64) 1.3 times the time, beyond that by the number.
+// A launch that leaves most of the chip idle is bound by its longest chain of blocks.  The constants below
+// are fitted to graph replays of la_fwd and la_bwd on 1 .. 128 scans of 64 .. 4096 tokens.
+struct ChainModel {
+    double launch;          // us: a launch (first loads, states, drain)
+    double lead, own, plain; // a block that only updates the state, a block of a piece, of the plain scan
+    double pre, round, seg; // pre-pass and segment scan at 512-token segments, per 128 tokens more, per segment
+    double unit;            // workgroups that run undisturbed: one to a compute unit (two of bf16 at d = 64)
+    double busy, until, slope; // beyond: the factor up to `until` units, then growing with their number
+    int shortest;           // piece
+};
+constexpr ChainModel kChain[2][2] = {   // [fp32, bf16][d = 64, 128]
+    {{2.5, 2.0, 4.1, 4.1, 34.0, 7.0, 0.06, kComputeUnits, 1.4, 4.0, 0.35, 32},
+     {3.0, 2.7, 5.8, 5.8, 46.0, 9.0, 0.07, kComputeUnits, 1.5, 2.0, 0.75, 32}},
+    {{4.2, 0.64, 0.87, 0.75, 9.0, 0.0, 0.03, 2 * kComputeUnits, 1.3, 2.0, 0.65, 64},
+     {5.0, 0.77, 1.2, 1.1, 14.0, 1.25, 0.07, kComputeUnits, 1.3, 2.0, 0.65, 64}}};
 // So the rule weighs the plan's chain against launch + leading blocks + own blocks of every piece length
 // and takes the best if the estimate is a tenth better.  Measured, la_fwd / la_bwd in us, plan -> rule:
 //   d = 128:  8 scans of 512 tokens  22.6 / 22.9 -> 16.8 / 17.1     16 of 1000  40.9 / 43.2 -> 29.4 / 32.9
 //             12 of 675              39.5 / 41.2 -> 21.3 / 23.1     5 of 1869, lambda = 0.9  35.1 / 38.0 -> 13.9 / 16.3
 //   d = 64:   11 of 597              25.0 / 26.8 -> 15.8 / 18.2     16 of 1215, lambda = 0.95  26.1 / 26.3 -> 18.1 / 20.7
+//   fp32, d = 128:  8 of 512  95.6 / 96.6 -> 50.8 / 52.4;  d = 64:  2 of 256  35.6 / 35.8 -> 20.2 / 20.4
 // (lambda = 1 or up to 0.9999 where none is given); on 70 shapes of 1 .. 200 scans it never lost more than 2 %.
 // Six LDS stages instead of three made the same launches 30 % slower.
 int rebuild_piece(const Plan &p, long scans, int H, int n, int d, la_dtype dt, int roles, const LaLambdas &lams,
@@ -504,16 +550,17 @@ int rebuild_piece(const Plan &p, long scans, int H, int n, int d, la_dtype dt, i
 {
     const auto on = [](const std::atomic<long> &x) { return x.load(std::memory_order_relaxed) != 0; };
     const long forced = g_sw.piece.load(std::memory_order_relaxed);
-    if (dt != LA_BF16 || forced < 0 || on(g_sw.lseg) || on(g_sw.staged_scan) || on(g_sw.staged_prepass) ||
+    if (forced < 0 || on(g_sw.lseg) || on(g_sw.f32_plain) || on(g_sw.staged_scan) || on(g_sw.staged_prepass) ||
         on(g_sw.no_trio) || on(g_sw.no_pair) || on(g_sw.ablate) || on(g_sw.store_policy))
         return 0;
     if (forced > 0) return round_up((int)(forced < p.L ? forced : p.L), 32);
-
-    const bool wide = d == 128;
-    const double launch = wide ? 5.0 : 4.2, lead = wide ? 0.77 : 0.64, own = wide ? 1.2 : 0.87, plain = wide ? 1.1 : 0.75;
-    const int unit = wide ? kComputeUnits : 2 * kComputeUnits;   // workgroups that run undisturbed
-    const auto load = [&](double wgs) { return wgs <= unit ? 1.0 : wgs <= 2 * unit ? 1.3 : 0.65 * wgs / unit; };
-    if ((double)roles * scans * p.S > 3.0 * unit) return 0;      // the chip is full: bound by bytes, not by the chain
+    const ChainModel &m = kChain[dt == LA_BF16 ? 1 : 0][d == 128 ? 1 : 0];
+    const auto load = [&](double wgs) {
+        const double q = wgs / m.unit;
+        return q <= 1.0 ? 1.0 : q <= m.until ? m.busy : m.slope * q;
+    };
+    const double most = 3.0 * m.unit;
+    if ((double)roles * scans * p.S > most) return 0;            // the chip is full: bound by throughput, not by the chain
 
     double reach = 0.0;                                          // rows a leading chain may need, at most
     for (int h = 0; h < H; ++h) {
@@ -521,16 +568,16 @@ int rebuild_piece(const Plan &p, long scans, int H, int n, int d, la_dtype dt, i
         if (r > reach) reach = r;
     }
     const double segs = (double)scans * p.S;
-    double best = launch + load(roles * segs) * (p.S > 1 ? p.L : n) / 32.0 * plain;
-    if (p.S > 1) best += (wide ? 14.0 + 1.25 * (p.L - 512) / 128 : 9.0) + (wide ? 0.07 : 0.03) * segs * (roles > 1 ? 2 : 1);
+    double best = m.launch + load(roles * segs) * (p.S > 1 ? p.L : n) / 32.0 * m.plain;
+    if (p.S > 1) best += m.pre + m.round * (p.L - 512) / 128 + m.seg * segs * (roles > 1 ? 2 : 1);
     best *= 0.9;
     int piece = 0;
-    for (int len = 64; len <= p.L; len *= 2) {
+    for (int len = m.shortest; len <= p.L; len *= 2) {
         const double wgs = (double)roles * scans * ((n + len - 1) / len);
         // (la_bwd_saved wants la_fwd's states at multiples of the plan's segments)
-        if (wgs > 3.0 * unit || (p.S > 1 && p.L % len != 0)) continue;
+        if (wgs > most || (p.S > 1 && p.L % len != 0)) continue;
         const double before = n - len < reach + 64 ? (n > len ? n - len : 0) : reach + 64;
-        const double t = launch + load(wgs) * (before / 32 * lead + (len < n ? len : n) / 32.0 * own);
+        const double t = m.launch + load(wgs) * (before / 32 * m.lead + (len < n ? len : n) / 32.0 * m.own);
         if (t < best) { best = t; piece = len; }
     }
     return piece;
@@ -606,8 +653,9 @@ int run_scan(const void *A, const void *Bm, const void *C, void *Out, const LaLa
     a.rev = REV ? 1 : 0;
     a.st_in = st_in;
     a.st_out = st_out;
-    const bool plain = a.act == 0 || a.act == LA_ACT_EXT;
-    if (dt == LA_BF16 && (d == 64 ? prepare_bf16<64>() : prepare_bf16<128>()) != hipSuccess) return LA_ERR_LAUNCH;
+    // (the fp32 kernel takes pieces with any activation or epilogue)
+    const bool plain = dt == LA_F32 || a.act == 0 || a.act == LA_ACT_EXT;
+    if (prepare(d, dt) != hipSuccess) return LA_ERR_LAUNCH;
     const int piece = !REV && plain ? rebuild_piece(p, scans, H, n, d, dt, 1, lams, a.skip_bits) : 0;
     if (piece > 0) {
         if (p.S > 1) { a.saved = a.states; a.saved_L = p.L; a.saved_S = p.S; }    // for la_bwd_saved
@@ -616,8 +664,7 @@ int run_scan(const void *A, const void *Bm, const void *C, void *Out, const LaLa
         ScanLaunch l = {};
         l.r[0] = a; l.nroles = 1; l.items = (int)(scans * a.S);
         ScopedTimer t(s);
-        const hipError_t e = d == 64 ? launch_bf16_rebuild<false, 64>(l, lams, s) : launch_bf16_rebuild<false, 128>(l, lams, s);
-        return e == hipSuccess ? LA_OK : LA_ERR_LAUNCH;
+        return launch_rebuild(l, lams, d, dt, s) == hipSuccess ? LA_OK : LA_ERR_LAUNCH;
     }
     if (p.S > 1) {
         int rc = run_prepass(&a, 1, lams, scans, d, dt, s);
@@ -695,16 +742,15 @@ int run_backward(const void *Q, const void *K, const void *V, const void *dO, vo
     }
     const int acts = pre[0].act | pre[1].act | av.act;
     const bool all_ext = pre[0].act == LA_ACT_EXT && pre[1].act == LA_ACT_EXT && av.act == LA_ACT_EXT;
-    if (dt == LA_BF16 && (d == 64 ? prepare_bf16<64>() : prepare_bf16<128>()) != hipSuccess) return LA_ERR_LAUNCH;
-    const int piece = !reuse && (acts == 0 || all_ext) ? rebuild_piece(p, scans, H, n, d, dt, 3, lams, av.skip_bits) : 0;
+    if (prepare(d, dt) != hipSuccess) return LA_ERR_LAUNCH;
+    const int piece = !reuse && (dt == LA_F32 || acts == 0 || all_ext) ? rebuild_piece(p, scans, H, n, d, dt, 3, lams, av.skip_bits) : 0;
     if (piece > 0) {
         ScanLaunch l;
         l.r[0] = pre[0]; l.r[1] = pre[1]; l.r[2] = av; l.nroles = 3;
         for (ScanArgs &r : l.r) { r.states = nullptr; r.L = piece; r.S = (n + piece - 1) / piece; }
         l.items = (int)(scans * l.r[0].S);
         ScopedTimer t(s);
-        const hipError_t e = d == 64 ? launch_bf16_rebuild<true, 64>(l, lams, s) : launch_bf16_rebuild<true, 128>(l, lams, s);
-        return e == hipSuccess ? LA_OK : LA_ERR_LAUNCH;
+        return launch_rebuild(l, lams, d, dt, s) == hipSuccess ? LA_OK : LA_ERR_LAUNCH;
     }
     if (p.S > 1) {
         int rc;

@@ -124,7 +124,9 @@ __device__ __forceinline__ float f32s_max3(float big, float a, float b)
     return big;
 }
 
-template <int D, bool STATE_ONLY>
+// REBUILD: short pieces whose workgroups first walk the blocks before their piece with the state update
+// alone, for launches that would leave most of the chip idle (see la_scan_bf16_dma).
+template <int D, bool STATE_ONLY, bool REBUILD = false>
 __global__ __launch_bounds__(2 * D, 2) void la_scan_f32s(ScanLaunch launch, LaLambdas lams)
 {
     using Cfg = F32sCfg<D>;
@@ -171,8 +173,22 @@ __global__ __launch_bounds__(2 * D, 2) void la_scan_f32s(ScanLaunch launch, LaLa
         if (rev && seg == 0) return;
     }
     const float lam = lams.v[scan % a.H], lg = lams.lg2[scan % a.H];
-    const int seg_lo = seg * a.L;
-    const int seg_hi = min(a.n, seg_lo + a.L);
+    int seg_lo = seg * a.L;
+    int seg_hi = min(a.n, seg_lo + a.L);
+    int nwarm = 0;                             // leading blocks that only update the state
+    bool from_start = true;                    // ... and whether they begin where the scan does
+    if (REBUILD) {
+        const int before = rev ? a.n - seg_hi : seg_lo;
+        int rows = before;
+        if (a.skip_bits > 0.f && lg < 0.f) {
+            const float reach = a.skip_bits / -lg;
+            if (reach < (float)before) rows = min(before, ((int)(reach / BK) + 2) * BK);
+        }
+        from_start = rows == before;
+        nwarm = (rows + BK - 1) / BK;
+        if (rev) seg_hi += rows;
+        else seg_lo -= rows;
+    }
     const int nblk = (seg_hi - seg_lo + BK - 1) / BK;
 
     const int bi = scan / a.H, hi = scan % a.H;
@@ -225,7 +241,9 @@ __global__ __launch_bounds__(2 * D, 2) void la_scan_f32s(ScanLaunch launch, LaLa
 
     // ---- running state St[i][j], j = 32 w + l32, in accumulator layout ---------------------
     f32x16_t st[MT_D];
-    const float *gIn = STATE_ONLY ? nullptr : la_entering_state(a, scan, seg, rev, lg, D * D);
+    const float *gIn = STATE_ONLY ? nullptr
+                       : REBUILD  ? (!rev && from_start && a.st_in ? a.st_in + (size_t)scan * (D * D) : nullptr)
+                                  : la_entering_state(a, scan, seg, rev, lg, D * D);
     float amax = 0.0f;
 #pragma unroll
     for (int mt = 0; mt < MT_D; ++mt) st[mt] = f32x16_t{0};
@@ -254,7 +272,7 @@ __global__ __launch_bounds__(2 * D, 2) void la_scan_f32s(ScanLaunch launch, LaLa
     // ---- global -> registers (rows past the segment end read the last row and are zeroed when
     // the block is staged) ---------------------------------------------------------------------
     float4 ra[2][2], rb[2][2], rc[2][2];
-    auto load_block = [&](int blk) {
+    auto load_block = [&](int blk, bool lead = false) {      // lead: no A tile
         const int t0 = seg_lo + blk * BK;
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
@@ -263,7 +281,7 @@ __global__ __launch_bounds__(2 * D, 2) void la_scan_f32s(ScanLaunch launch, LaLa
             const float4 *pc = (const float4 *)(gC + row * ldC + 8 * sch);
             rb[u][0] = pb[0]; rb[u][1] = pb[1];
             rc[u][0] = pc[0]; rc[u][1] = pc[1];
-            if (!STATE_ONLY) {
+            if (!STATE_ONLY && !(REBUILD && lead)) {
                 const float4 *pa = (const float4 *)(gA + row * ldA + 8 * sch);
                 ra[u][0] = pa[0]; ra[u][1] = pa[1];
             }
@@ -296,7 +314,7 @@ __global__ __launch_bounds__(2 * D, 2) void la_scan_f32s(ScanLaunch launch, LaLa
         x[4] = r[1].x; x[5] = r[1].y; x[6] = r[1].z; x[7] = r[1].w;
     };
     // registers -> LDS, split; returns the largest magnitude staged by this thread
-    auto stage_split = [&]() -> float {
+    auto stage_split = [&](bool lead = false) -> float {
         float big = 0.0f;
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
@@ -320,7 +338,7 @@ __global__ __launch_bounds__(2 * D, 2) void la_scan_f32s(ScanLaunch launch, LaLa
             };
             put(rb[u], sB);
             put(rc[u], sC);
-            if (!STATE_ONLY) put(ra[u], sA);
+            if (!STATE_ONLY && !(REBUILD && lead)) put(ra[u], sA);
         }
         return big;
     };
@@ -363,21 +381,37 @@ __global__ __launch_bounds__(2 * D, 2) void la_scan_f32s(ScanLaunch launch, LaLa
     // weighted lambda^(m-1-r) and decays the old state by lambda^m
     const auto rows_of = [&](int t0) { return (want_final && t0 + BK > seg_hi) ? seg_hi - t0 : BK; };
     const bool any_act = (a.act & (LA_ACT_A | LA_ACT_BM | LA_ACT_C)) != 0;
+    // REBUILD: the state entering a multiple of saved_L, to the slot where la_entering_state looks for it
+    const int own_lo = seg_lo + (REBUILD && !rev ? nwarm * BK : 0);
+    const bool state_due = REBUILD && !rev && a.saved != nullptr && own_lo % a.saved_L == 0;
+    auto save_state = [&]() {
+        const int s0 = own_lo / a.saved_L;
+        const bool chain_free = a.skip_bits > 0.f && -lg * (float)a.saved_L >= a.skip_bits;
+        if (chain_free && s0 == 0) return;
+        float *p = a.saved + ((size_t)scan * a.saved_S + (chain_free ? s0 - 1 : s0)) * (size_t)(D * D) +
+                   4 * g * D + 32 * w + l32;
+#pragma unroll
+        for (int mt = 0; mt < MT_D; ++mt)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) p[(32 * mt + 8 * (v >> 2) + (v & 3)) * D] = st[mt][v];
+    };
     int ib = ib0;
-    if (ib < nblk) load_block(blk_of(ib));
+    if (ib < nblk) load_block(blk_of(ib), ib < nwarm);
     for (; ib < nblk; ++ib) {
+        const bool lead = REBUILD && ib < nwarm;
+        if (REBUILD && state_due && ib == nwarm) save_state();
         const int t0 = seg_lo + blk_of(ib) * BK, m_rows = rows_of(t0);
         // the lane's address terms are derived anew in every block (an XOR or an add each) instead of
         // living in a register per address for the whole loop, which would leave none for the prefetch
         asm volatile("" : "+v"(l32), "+v"(g), "+v"(ro_base), "+v"(ro_sw), "+v"(tr_base), "+v"(tr_sw), "+v"(srow), "+v"(sch));
         if (t0 + BK > seg_hi) pad_block(t0);
         if (any_act) act_block();
-        if (!(stage_split() < kF32sTileMax)) *sFlag = 1;
+        if (!(stage_split(lead) < kF32sTileMax)) *sFlag = 1;
         __syncthreads();                                     // tiles staged
         if (__builtin_amdgcn_readfirstlane(*sFlag) != 0) break;
-        if (ib + 1 < nblk) load_block(blk_of(ib + 1));
+        if (ib + 1 < nblk) load_block(blk_of(ib + 1), ib + 1 < nwarm);
         f32x16_t x = {0};
-        if (!STATE_ONLY) {
+        if (!STATE_ONLY && !lead) {
             // ---- this wave's share of the scores: S^T (lane = q, registers = keys) over 32 features
             f32x16_t s = {0};
             {
@@ -536,8 +570,11 @@ __global__ __launch_bounds__(2 * D, 2) void la_scan_f32s(ScanLaunch launch, LaLa
     // ---- the fp32 form, from the first block out of range on (v_mfma_f32_32x32x2_f32: A operand
     // A[l%32][l/32], B operand B[l/32][l%32]), single floats from row-major tiles; register v of a
     // state tile pairs rows i and i + 4
+    // (a leading block that meets its end here has its result computed too, and not stored)
     if (ib < nblk) load_block(blk_of(ib));
-    for (; ib < nblk; ++ib) {
+    for (int first = ib; ib < nblk; ++ib) {
+        const bool lead = REBUILD && ib < nwarm;
+        if (REBUILD && state_due && ib == nwarm && ib > first) save_state();
         const int t0 = seg_lo + blk_of(ib) * BK, m_rows = rows_of(t0);
         if (t0 + BK > seg_hi) pad_block(t0);
         if (any_act) act_block();
@@ -579,7 +616,7 @@ __global__ __launch_bounds__(2 * D, 2) void la_scan_f32s(ScanLaunch launch, LaLa
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int t = t0 + 8 * (v >> 2) + 4 * g + (v & 3);
-                if (t < seg_hi) {
+                if (t < seg_hi && !lead) {
                     float o = acc[v];
                     if (a.act & LA_ACT_OUT) o *= la_swish_grad(gE[(size_t)t * ldE + 32 * w + l32]);
                     if (a.act & LA_ACT_ACC) o += gO[(size_t)t * ldO + 32 * w + l32];
