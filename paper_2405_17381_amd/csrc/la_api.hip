@@ -303,7 +303,8 @@ hipError_t prepare_bf16()
     static std::once_flag once;
     static hipError_t err = hipSuccess;
     std::call_once(once, [&] {
-        const size_t scan = DmaCfg<3, D>::lds_bytes, pre = DmaPrepassCfg<4, D>::lds_bytes;
+        const size_t scan = DmaCfg<3, D>::lds_bytes, pre = DmaPrepassCfg<4, D>::lds_bytes,
+                     tiles = TilesPrepassCfg<D>::lds_bytes;
         const hipError_t all[] = {
             allow_lds(la_scan_bf16_dma<false, true, 0, 3, false, false, D>, scan),
             allow_lds(la_scan_bf16_dma<false, true, 0, 3, false, true, D>, scan),
@@ -311,7 +312,8 @@ hipError_t prepare_bf16()
             allow_lds(la_scan_bf16_dma<false, true, 0, 3, true, true, D>, scan),
             allow_lds(la_scan_bf16_dma<false, true, 0, 3, false, true, D, true>, scan),
             allow_lds(la_scan_bf16_dma<false, true, 0, 3, true, true, D, true>, scan),
-            allow_lds(la_prepass_bf16_dma<4, false, D>, pre), allow_lds(la_prepass_bf16_dma<4, true, D>, pre)};
+            allow_lds(la_prepass_bf16_dma<4, false, D>, pre), allow_lds(la_prepass_bf16_dma<4, true, D>, pre),
+            allow_lds(la_prepass_bf16_tiles<false, D>, tiles), allow_lds(la_prepass_bf16_tiles<true, D>, tiles)};
         for (const hipError_t e : all)
             if (e != hipSuccess) err = e;
     });
@@ -327,6 +329,16 @@ hipError_t launch_prepass_bf16_dma(const ScanLaunch &a, const LaLambdas &lams, h
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [&] { attr_err = allow_lds(kern, Cfg::lds_bytes); });
     if (attr_err != hipSuccess) return attr_err;
+    dim3 grid((unsigned)(a.items * a.nroles)), block(Cfg::NT);
+    hipLaunchKernelGGL(kern, grid, block, Cfg::lds_bytes, s, a, lams);
+    return hipGetLastError();
+}
+
+template <bool STRIDED, int D>
+hipError_t launch_prepass_bf16_tiles(const ScanLaunch &a, const LaLambdas &lams, hipStream_t s)
+{
+    using Cfg = TilesPrepassCfg<D>;
+    auto kern = la_prepass_bf16_tiles<STRIDED, D>;           // attributes: prepare_bf16
     dim3 grid((unsigned)(a.items * a.nroles)), block(Cfg::NT);
     hipLaunchKernelGGL(kern, grid, block, Cfg::lds_bytes, s, a, lams);
     return hipGetLastError();
@@ -429,15 +441,18 @@ template <bool REV, bool STATE_ONLY, int D>
 hipError_t launch_bf16_direct(const ScanLaunch &a, const LaLambdas &lams, bool strided, hipStream_t s)
 {
     if (STATE_ONLY) {
-        if (strided) return launch_prepass_bf16_dma<4, true, D>(a, lams, s);
         if constexpr (D == 128) {
-            switch (g_sw.prepass_groups.load(std::memory_order_relaxed)) {
-            case 1: return launch_prepass_bf16_dma<1, false, D>(a, lams, s);
-            case 2: return launch_prepass_bf16_dma<2, false, D>(a, lams, s);
-            default: break;
-            }
+            const long groups = strided ? 0 : g_sw.prepass_groups.load(std::memory_order_relaxed);
+            if (groups == 1) return launch_prepass_bf16_dma<1, false, D>(a, lams, s);
+            if (groups == 2) return launch_prepass_bf16_dma<2, false, D>(a, lams, s);
         }
-        return launch_prepass_bf16_dma<4, false, D>(a, lams, s);
+        // Short segments: one chain and nothing to add at its end; long ones: the chain in four groups.
+        // Measured on 16 scans, us at 512 / 1024 / 2048 tokens: d = 128 11.5 / 18 / 32 against 13.2 / 18 / 28;
+        // d = 64 7.5 against 7.6 at 512 with twice the slope.  (512 segments of 2048 tokens, memory-bound:
+        // la_fwd + la_bwd at (1, 16, 65536, 128) 0.887 against 0.877 ms; 320 of 512: 0.206 against 0.222.)
+        if (a.r[0].L <= (D == 128 ? 1024 : 512))
+            return strided ? launch_prepass_bf16_tiles<true, D>(a, lams, s) : launch_prepass_bf16_tiles<false, D>(a, lams, s);
+        return strided ? launch_prepass_bf16_dma<4, true, D>(a, lams, s) : launch_prepass_bf16_dma<4, false, D>(a, lams, s);
     }
     return strided ? launch_bf16_dma<REV, true, D>(a, lams, s) : launch_bf16_dma<REV, false, D>(a, lams, s);
 }

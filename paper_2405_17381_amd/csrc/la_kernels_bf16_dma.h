@@ -779,3 +779,170 @@ __global__ __launch_bounds__(2 * D_ * G_, 1) void la_prepass_bf16_dma(ScanLaunch
             gSt[(size_t)i * D + 32 * w + l32] = st[mt][v];
         }
 }
+
+// ---- the pre-pass of short segments: one chain, the state spread over all waves ----------------------
+// Same sums as la_prepass_bf16_dma, another split of the work.  There a wave holds a whole 32-column slice of
+// the state and the blocks are dealt out to four groups of waves, whose partial states (64 KB each) must be
+// added through LDS at the end: 4 of the 8 us that a workgroup takes besides its rounds, and 128 KB of LDS and
+// 1024 threads leave room for one workgroup per compute unit, so that 300 segments take two turns.  Here every
+// wave holds half a slice (two 32 x 32 tiles at d = 128) and all of them work on the same 64 rows at a time:
+// nothing is added at the end, 64 KB of LDS and 512 threads, two workgroups to a compute unit.  A step's
+// fragments are read into registers at once, so that its stage is refilled while they are multiplied.
+// Measured: 2 x 16 scans of 5003 tokens in 512-token segments at d = 128, pre-pass of la_fwd / la_bwd
+// 25 / 42 -> 18 / 32 us; a lone segment of 64 tokens 9.4 -> 5.7 us.  A step of 64 rows takes 0.83 us against
+// 0.63 in the four groups, whose kernel therefore keeps the long segments.
+template <int D_>
+struct TilesPrepassCfg {
+    static constexpr int D = D_, ROWS = 64, NS = 2, NW = D / 32, NT = 128 * NW;
+    static constexpr int PITCH = 2 * D, CPR = D / 8, RPI = 64 / CPR;
+    static constexpr int TILE_BYTES = ROWS * D * 2;
+    static constexpr int STAGE_BYTES = 2 * TILE_BYTES;       // Bm, C
+    static constexpr size_t lds_bytes = (size_t)NS * STAGE_BYTES;
+};
+
+template <bool STRIDED, int D_>
+__global__ __launch_bounds__(4 * D_, 4) void la_prepass_bf16_tiles(ScanLaunch launch, LaLambdas lams)
+{
+    using Cfg = TilesPrepassCfg<D_>;
+    constexpr int D = Cfg::D, ROWS = Cfg::ROWS, NW = Cfg::NW, PITCH = Cfg::PITCH, CPR = Cfg::CPR, RPI = Cfg::RPI;
+    constexpr int SW8 = dma_swz<D>(8);
+    constexpr int KS = ROWS / 16, MTH = D / 64;              // k-steps per step; state tiles per wave
+
+    extern __shared__ __align__(16) unsigned char smem_dma[];
+
+    const int tid = threadIdx.x;
+    const int l = tid & 63, l32 = l & 31, g = l >> 5;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int w = wv % NW, m0 = (wv / NW) * MTH;             // value-feature slice, first row tile
+
+    const int role = launch.nroles == 2 ? (int)(blockIdx.x / launch.items) : 0;
+    const int item = launch.nroles == 2 ? (int)(blockIdx.x % launch.items) : (int)blockIdx.x;
+    const ScanArgs &a = launch.r[role];
+    const int seg = item % a.S;
+    const int bh = item / a.S;                               // (head in dispatch order, batch)
+    const int scan = (bh % a.B) * a.H + lams.order[bh / a.B];
+    const bool rev = a.rev != 0;
+    if (!rev && seg == a.S - 1) return;                      // never consumed
+    if (rev && seg == 0) return;
+
+    const float lg = lams.lg2[scan % a.H];
+    auto pw = [lg](int k) -> float { return exp2f((float)k * lg); };
+
+    const int seg_lo = seg * a.L;
+    const int seg_hi = min(a.n, seg_lo + a.L);
+    const int nstep = (seg_hi - seg_lo + ROWS - 1) / ROWS;
+    int is0 = 0;                                             // decay cut-off
+    if (a.skip_bits > 0.f && lg < 0.f) {
+        const float reach = a.skip_bits / -lg;
+        if (reach < (float)(nstep * ROWS)) is0 = max(0, nstep - ((int)(reach / ROWS) + 2));
+    }
+
+    const uint16_t *gB, *gC;
+    int ldB, ldC;
+    if (STRIDED) {
+        const long bb = scan / a.H, hh = scan % a.H;
+        gB = (const uint16_t *)a.Bm + bb * a.lB.bs + hh * a.lB.hs;
+        gC = (const uint16_t *)a.C + bb * a.lC.bs + hh * a.lC.hs;
+        ldB = a.lB.ld; ldC = a.lC.ld;
+    } else {
+        const size_t base = (size_t)scan * a.n * D;
+        gB = (const uint16_t *)a.Bm + base;
+        gC = (const uint16_t *)a.C + base;
+        ldB = ldC = D;
+    }
+
+    float wt[16];                              // weight of the token in slot (ks, e) inside 32 rows
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int key = 8 * (v >> 2) + 4 * g + (v & 3);
+        wt[v] = rev ? pw(key) : pw(31 - key);
+    }
+    const int a4 = l & 3, b4 = (l >> 2) & 3, h16 = (l >> 4) & 1;
+    const int tr_base = (4 * g + b4) * PITCH + 8 * (a4 & 1);
+    const int tr_sw = (2 * h16 + (a4 >> 1)) ^ dma_swz<D>(4 * g + b4);
+    int dma_row[2], dma_col[2];                              // (ROWS / RPI) / waves = 2 load slots per wave and tile
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        dma_row[j] = RPI * (2 * wv + j) + l / CPR;
+        dma_col[j] = 8 * ((l % CPR) ^ dma_swz<D>(dma_row[j]));
+    }
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(la_lds_void *)smem_dma);
+
+    f32x16_t st[MTH];
+#pragma unroll
+    for (int m = 0; m < MTH; ++m) st[m] = f32x16_t{0};
+
+    const auto blk_of = [&](int is) { return rev ? (nstep - 1 - is) : is; };
+    auto issue = [&](int is, int stage) {
+        const int t0 = seg_lo + blk_of(is) * ROWS;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const size_t row = (size_t)min(t0 + dma_row[j], seg_hi - 1);
+            const uint32_t dst = lds0 + stage * Cfg::STAGE_BYTES + (2 * wv + j) * 1024;
+            dma_load16<true>(gB + row * ldB + dma_col[j], dst);
+            dma_load16<true>(gC + row * ldC + dma_col[j], dst + Cfg::TILE_BYTES);
+        }
+    };
+    auto tr_read = [&](const unsigned char *s, int ks, int mt, U2 (&r)[2]) {
+        const unsigned char *p = s + tr_base + 16 * ks * PITCH;
+        r[0] = lds_read_tr(p + (((4 * mt) ^ tr_sw) << 4));
+        r[1] = lds_read_tr(p + 8 * PITCH + (((4 * mt) ^ tr_sw ^ SW8) << 4));
+    };
+
+    if (is0 < nstep) issue(is0, 0);
+    if (is0 + 1 < nstep) issue(is0 + 1, 1);
+    for (int is = is0; is < nstep; ++is) {
+        const int stage = (is - is0) & 1;
+        unsigned char *sb = smem_dma + stage * Cfg::STAGE_BYTES;
+        const int blk = blk_of(is), t0 = seg_lo + blk * ROWS;
+        if (is + 1 < nstep) la_wait_vm<4>();    // only the next step's four loads are younger
+        else la_wait_vm<0>();
+        if (t0 + ROWS > seg_hi) {               // partial step: zero padding (exact)
+            const U4 z = {0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                if (t0 + dma_row[j] >= seg_hi) {
+                    unsigned char *dst = sb + (2 * wv + j) * 1024 + 16 * l;
+                    *(U4 *)dst = z;
+                    *(U4 *)(dst + Cfg::TILE_BYTES) = z;
+                }
+        }
+        LA_LDS_BARRIER();                       // landed for every wave
+        U2 rc[KS][2], rb[MTH][KS][2];
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) tr_read(sb + Cfg::TILE_BYTES, ks, w, rc[ks]);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int m = 0; m < MTH; ++m) tr_read(sb, ks, m0 + m, rb[m][ks]);
+        if (is + 2 < nstep) {
+            LA_LDS_BARRIER();                   // every wave has its fragments: the stage is free
+            issue(is + 2, stage);
+        }
+        LA_BATCH_FENCE();
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            // distance of these 32 rows to the segment's far end, folded into the weights
+            // (forward: never the last segment, so the segment is a whole number of steps)
+            const int row0 = blk * ROWS + 32 * (ks >> 1);
+            const float mu = rev ? pw(row0) : pw(seg_hi - seg_lo - 32 - row0);
+            const U4 cf = {rc[ks][0][0], rc[ks][0][1], rc[ks][1][0], rc[ks][1][1]};
+            U4 cw;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                cw[e] = pack2_bf16(bf16_lo(cf[e]) * (wt[8 * (ks & 1) + 2 * e] * mu),
+                                   bf16_hi(cf[e]) * (wt[8 * (ks & 1) + 2 * e + 1] * mu));
+#pragma unroll
+            for (int m = 0; m < MTH; ++m) {
+                const U4 bt = {rb[m][ks][0][0], rb[m][ks][0][1], rb[m][ks][1][0], rb[m][ks][1][1]};
+                st[m] = mfma32(bt, cw, st[m]);
+            }
+        }
+    }
+
+    float *gSt = a.states + ((size_t)scan * a.S + seg) * (size_t)(D * D) + 32 * w + l32;
+#pragma unroll
+    for (int m = 0; m < MTH; ++m)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) gSt[(32 * (m0 + m) + 8 * (v >> 2) + 4 * g + (v & 3)) * D] = st[m][v];
+}
