@@ -1192,7 +1192,7 @@ int la_lrpe_rotate_bwd(const void *X, const float *theta, const void *dXw, void 
     hipStream_t s = (hipStream_t)hip_stream;
     rc = run_lrpe<true>(a, B, d, dt, s);
     if (rc != LA_OK) return rc;
-    hipLaunchKernelGGL(la_lrpe_theta_reduce, dim3((unsigned)(H * d / 32)), dim3(256), 0, s,
+    hipLaunchKernelGGL(la_lrpe_theta_reduce, dim3((unsigned)(H * d / 32)), dim3(32 * LRPE_SLICES), 0, s,
                        (const float *)workspace, dtheta, B, H, a.tiles, d, accumulate_dtheta ? 1 : 0);
     return hipGetLastError() == hipSuccess ? LA_OK : LA_ERR_LAUNCH;
 }

@@ -137,33 +137,36 @@ __global__ __launch_bounds__(256) void la_lrpe_rotate_kernel(LrpeArgs a)
 }
 
 // dtheta[h, i] = (accumulate ? dtheta[h, i] : 0) + sum over b and tiles of the partials, in fp64
-// and in a fixed order: 8 threads per (head, feature) each add every 8th partial, then one of
-// them adds the 8 sums.  A workgroup covers 32 consecutive (head, feature) entries.
-__global__ __launch_bounds__(256) void la_lrpe_theta_reduce(const float *partial, float *dtheta, int B, int H,
-                                                            int tiles, int D, int accumulate)
+// and in a fixed order: 32 threads per (head, feature) each add every 32nd partial, then one of
+// them adds the 32 sums.  A workgroup covers 32 consecutive (head, feature) entries.  Bound by the latency
+// of its few loads: with 8 threads per entry and eight loads in flight, 512 partials took 31 us (64
+// workgroups of 64 loads a thread, in eight turns), with 32 and sixteen loads 8 us.
+constexpr int LRPE_SLICES = 32;
+__global__ __launch_bounds__(32 * LRPE_SLICES) void la_lrpe_theta_reduce(const float *partial, float *dtheta, int B,
+                                                                          int H, int tiles, int D, int accumulate)
 {
-    __shared__ double red[8][32];
+    __shared__ double red[LRPE_SLICES][32];
     const int lane = threadIdx.x % 32, slice = threadIdx.x / 32;
     const int e = blockIdx.x * 32 + lane;              // h * D + i  (H * D is a multiple of 32)
     const int h = e / D, i = e % D;
     const int count = B * tiles;
     double sum = 0.0;
-    for (int idx0 = slice; idx0 < count; idx0 += 64) {
-        float v[8];
+    for (int idx0 = slice; idx0 < count; idx0 += 16 * LRPE_SLICES) {
+        float v[16];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {                  // eight loads in flight
-            const int idx = idx0 + 8 * j;
+        for (int j = 0; j < 16; ++j) {                 // sixteen loads in flight
+            const int idx = min(idx0 + LRPE_SLICES * j, count - 1);
             const int b = idx / tiles, k = idx % tiles;
-            v[j] = idx < count ? partial[(((size_t)b * H + h) * tiles + k) * D + i] : 0.f;
+            v[j] = partial[(((size_t)b * H + h) * tiles + k) * D + i];
         }
 #pragma unroll
-        for (int j = 0; j < 8; ++j) sum += (double)v[j];
+        for (int j = 0; j < 16; ++j) sum += idx0 + LRPE_SLICES * j < count ? (double)v[j] : 0.0;
     }
     red[slice][lane] = sum;
     __syncthreads();
     if (slice == 0) {
         double total = accumulate ? (double)dtheta[e] : 0.0;
-        for (int r = 0; r < 8; ++r) total += red[r][lane];
+        for (int r = 0; r < LRPE_SLICES; ++r) total += red[r][lane];
         dtheta[e] = (float)total;
     }
 }
