@@ -530,7 +530,6 @@ ScanArgs make_args(const void *A, const void *Bm, const void *C, void *Out, cons
     a.st_out = nullptr;
     a.act = 0;
     a.E = nullptr;
-    a.saved = nullptr; a.saved_L = 1; a.saved_S = 0;
     return a;
 }
 
@@ -673,10 +672,11 @@ int run_scan(const void *A, const void *Bm, const void *C, void *Out, const LaLa
     if (prepare(d, dt) != hipSuccess) return LA_ERR_LAUNCH;
     const int piece = !REV && plain ? rebuild_piece(p, scans, H, n, d, dt, 1, lams, a.skip_bits) : 0;
     if (piece > 0) {
-        if (p.S > 1) { a.saved = a.states; a.saved_L = p.L; a.saved_S = p.S; }    // for la_bwd_saved
+        ScanLaunch l = {};
+        l.saved = p.S > 1 ? a.states : nullptr;              // for la_bwd_saved
+        l.saved_L = p.L; l.saved_S = p.S;
         a.states = nullptr;
         a.L = piece; a.S = (n + piece - 1) / piece;
-        ScanLaunch l = {};
         l.r[0] = a; l.nroles = 1; l.items = (int)(scans * a.S);
         ScopedTimer t(s);
         return launch_rebuild(l, lams, d, dt, s) == hipSuccess ? LA_OK : LA_ERR_LAUNCH;
@@ -760,7 +760,7 @@ int run_backward(const void *Q, const void *K, const void *V, const void *dO, vo
     if (prepare(d, dt) != hipSuccess) return LA_ERR_LAUNCH;
     const int piece = !reuse && (dt == LA_F32 || acts == 0 || all_ext) ? rebuild_piece(p, scans, H, n, d, dt, 3, lams, av.skip_bits) : 0;
     if (piece > 0) {
-        ScanLaunch l;
+        ScanLaunch l = {};
         l.r[0] = pre[0]; l.r[1] = pre[1]; l.r[2] = av; l.nroles = 3;
         for (ScanArgs &r : l.r) { r.states = nullptr; r.L = piece; r.S = (n + piece - 1) / piece; }
         l.items = (int)(scans * l.r[0].S);
@@ -783,7 +783,7 @@ int run_backward(const void *Q, const void *K, const void *V, const void *dO, vo
                              !g_sw.ablate.load(std::memory_order_relaxed)
                        : !g_sw.f32_plain.load(std::memory_order_relaxed));
     if (one_launch) {
-        ScanLaunch l;
+        ScanLaunch l = {};
         l.r[0] = pre[0]; l.r[1] = pre[1]; l.r[2] = av; l.nroles = 3; l.items = (int)(scans * p.S);
         ScopedTimer t(s);
         hipError_t e;

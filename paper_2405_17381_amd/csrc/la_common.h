@@ -74,8 +74,6 @@ struct ScanArgs {
                          // as they are staged) and whether Out is a pre-activation gradient
     const void *E;       // LA_ACT_OUT: the pre-activation whose gradient Out is, [scans, n, D]
     LaLayout lA, lB, lC, lO, lE;   // layouts of A, Bm, C, Out, E
-    float *saved;        // block scans that rebuild their entering states: where to leave those at
-    int saved_L, saved_S; // multiples of saved_L rows ([scans, saved_S, D, D]; nullptr: nowhere)
 };
 
 // Swish on the query / key projections (Sec. 4.2: Q = phi(X W_q), K = phi(X W_k)).
@@ -113,6 +111,8 @@ struct ScanLaunch {
                          // scan: r[0] forward in time (dQ), r[1] and r[2] reversed (dK, dV), the three
                          // workgroups of an item on one XCD (id % 8), roles in consecutive slots
     int items;           // scans * S
+    float *saved;        // block scans that rebuild their entering states: where to leave those at
+    int saved_L, saved_S; // multiples of saved_L rows ([scans, saved_S, D, D]; nullptr: nowhere)
 };
 
 // kernel arguments travel in the dispatch packet: 4 KB at most

@@ -155,7 +155,7 @@ __device__ __forceinline__ U2 lds_read_tr(const unsigned char *p)
 //   order (as far back as the decay cut-off reaches) with the state update alone, no A tile, no result,
 //   so that no pre-pass and no segment scan run first and pieces may be shorter than what segment
 //   states in scratch would allow.  ScanArgs::L is the piece, S the pieces per scan, `states` unused;
-//   `saved` (if any) receives the states at multiples of saved_L, as the segment scan leaves them.
+//   ScanLaunch::saved (if any) receives the states at multiples of saved_L, as the segment scan leaves them.
 template <bool REV_, bool NT_STORE, int ABL, int NS_, bool TRIO = false, bool STRIDED = false, int D_ = 128,
           bool REBUILD = false>
 __global__ __launch_bounds__(2 * D_, NS_ <= 3 ? 2 : 1) void la_scan_bf16_dma(ScanLaunch launch, LaLambdas lams)
@@ -282,8 +282,11 @@ __global__ __launch_bounds__(2 * D_, NS_ <= 3 ? 2 : 1) void la_scan_bf16_dma(Sca
     const float *gSt = REBUILD ? (!REV && from_start && a.st_in ? a.st_in + (size_t)scan * (D * D) : nullptr)
                                : la_entering_state(a, scan, seg, REV, lg, D * D);
     const bool has_init = gSt != nullptr;
-    if (!REBUILD && has_init && a.transpose_init) {
-        // the stored state is that of the scan with Bm and C exchanged: through LDS, transposed
+    if (!REBUILD && has_init && (a.transpose_init || TRIO)) {
+        // the stored state is that of the scan with Bm and C exchanged: through LDS, transposed (in a
+        // trio the other roles take the same road, so that the workgroups of an item start in step and
+        // the later readers of a tile still find it in L2: 0.4 % of la_bwd at (1, 16, 65536, 128))
+        const int si = a.transpose_init ? 1 : D + 1, sj = a.transpose_init ? D + 1 : 1;
         float *sT = reinterpret_cast<float *>(smem_dma);         // [D][D+1]
         for (int e = tid * 4; e < D * D; e += 4 * Cfg::NT) {
             const float4 x = *(const float4 *)(gSt + e);
@@ -296,7 +299,7 @@ __global__ __launch_bounds__(2 * D_, NS_ <= 3 ? 2 : 1) void la_scan_bf16_dma(Sca
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int i = 32 * mt + 8 * (v >> 2) + 4 * g + (v & 3);
-                st[mt][v] = sT[(32 * w + l32) * (D + 1) + i];
+                st[mt][v] = sT[(32 * w + l32) * sj + i * si];
             }
         __syncthreads();
     } else if (has_init) {                      // (a condition per element would be a branch per load)
@@ -305,6 +308,8 @@ __global__ __launch_bounds__(2 * D_, NS_ <= 3 ? 2 : 1) void la_scan_bf16_dma(Sca
         for (int mt = 0; mt < MT_D; ++mt)
 #pragma unroll
             for (int v = 0; v < 16; ++v) st[mt][v] = p[(32 * mt + 8 * (v >> 2) + (v & 3)) * D];
+        __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0) here, or the compiler waits for them in the block
+                                                // loop, in every iteration, and for the tiles in flight too
     } else {
 #pragma unroll
         for (int mt = 0; mt < MT_D; ++mt)
@@ -359,12 +364,12 @@ __global__ __launch_bounds__(2 * D_, NS_ <= 3 ? 2 : 1) void la_scan_bf16_dma(Sca
 
     // REBUILD: the state entering a multiple of saved_L, to the slot where la_entering_state looks for it
     const int own_lo = seg_lo + (REBUILD && !REV ? nwarm * BK : 0);
-    const bool seg_state_due = REBUILD && !REV && a.saved != nullptr && own_lo % a.saved_L == 0;
+    const bool seg_state_due = REBUILD && !REV && launch.saved != nullptr && own_lo % launch.saved_L == 0;
     auto save_state = [&]() {
-        const int s0 = own_lo / a.saved_L;
-        const bool chain_free = a.skip_bits > 0.f && -lg * (float)a.saved_L >= a.skip_bits;
+        const int s0 = own_lo / launch.saved_L;
+        const bool chain_free = a.skip_bits > 0.f && -lg * (float)launch.saved_L >= a.skip_bits;
         if (chain_free && s0 == 0) return;
-        float *p = a.saved + ((size_t)scan * a.saved_S + (chain_free ? s0 - 1 : s0)) * (size_t)(D * D) +
+        float *p = launch.saved + ((size_t)scan * launch.saved_S + (chain_free ? s0 - 1 : s0)) * (size_t)(D * D) +
                    4 * g * D + 32 * w + l32;
 #pragma unroll
         for (int mt = 0; mt < MT_D; ++mt)

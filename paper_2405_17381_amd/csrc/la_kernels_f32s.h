@@ -383,12 +383,12 @@ __global__ __launch_bounds__(2 * D, 2) void la_scan_f32s(ScanLaunch launch, LaLa
     const bool any_act = (a.act & (LA_ACT_A | LA_ACT_BM | LA_ACT_C)) != 0;
     // REBUILD: the state entering a multiple of saved_L, to the slot where la_entering_state looks for it
     const int own_lo = seg_lo + (REBUILD && !rev ? nwarm * BK : 0);
-    const bool state_due = REBUILD && !rev && a.saved != nullptr && own_lo % a.saved_L == 0;
+    const bool state_due = REBUILD && !rev && launch.saved != nullptr && own_lo % launch.saved_L == 0;
     auto save_state = [&]() {
-        const int s0 = own_lo / a.saved_L;
-        const bool chain_free = a.skip_bits > 0.f && -lg * (float)a.saved_L >= a.skip_bits;
+        const int s0 = own_lo / launch.saved_L;
+        const bool chain_free = a.skip_bits > 0.f && -lg * (float)launch.saved_L >= a.skip_bits;
         if (chain_free && s0 == 0) return;
-        float *p = a.saved + ((size_t)scan * a.saved_S + (chain_free ? s0 - 1 : s0)) * (size_t)(D * D) +
+        float *p = launch.saved + ((size_t)scan * launch.saved_S + (chain_free ? s0 - 1 : s0)) * (size_t)(D * D) +
                    4 * g * D + 32 * w + l32;
 #pragma unroll
         for (int mt = 0; mt < MT_D; ++mt)
