@@ -903,6 +903,53 @@ int check_wide(int dk, int dv)
     return LA_OK;
 }
 
+// la_fwd_wide in bf16 with d_k = 256, d_v = 128 (arguments not yet checked beyond shape, type, Qw and Kw).
+int forward_wide(const void *Qw, const void *Kw, const void *V, const float *lambda, void *O, const Plan &plan,
+                 int B, int H, int n, void *workspace, size_t workspace_bytes, hipStream_t s)
+{
+    constexpr int DK = DmaWideCfg::DK, DV = DmaWideCfg::DV;
+    if (!V || !O || !lambda) return LA_ERR_NULL;
+    if (!aligned16(Qw) || !aligned16(Kw) || !aligned16(V) || !aligned16(O)) return LA_ERR_ALIGN;
+    LaLambdas lams;
+    int rc = check_lambda(lambda, H, &lams);
+    if (rc != LA_OK) return rc;
+    rc = check_workspace(plan, B, H, DV, workspace, workspace_bytes, false);
+    if (rc != LA_OK) return rc;
+    static std::once_flag once;
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(once, [&] { attr_err = allow_lds(la_scan_bf16_dma_wide, DmaWideCfg::lds_bytes); });
+    if (attr_err != hipSuccess || prepare(DV, LA_BF16) != hipSuccess) return LA_ERR_LAUNCH;
+
+    const long scans = (long)B * H;
+    Plan p = plan;
+    if (plan.S > 1) {                            // at most S / 2 segments: two sets of states in the plan's scratch
+        p.L = round_up((int)(((long)n + plan.S / 2 - 1) / (plan.S / 2)), 64);
+        p.S = (int)(((long)n + p.L - 1) / p.L);
+    }
+    ScanLaunch l = {};
+    l.r[0] = make_args(Qw, Kw, V, O, p, H, n, DV, LA_BF16, (float *)workspace, 0);
+    l.r[0].B = B;
+    l.nroles = 1; l.items = (int)(scans * p.S);
+    if (p.S > 1) {
+        order_heads(&lams, H);
+        const size_t set = (size_t)scans * p.S * DV * DV;
+        ScanArgs pre[2] = {l.r[0], l.r[0]};      // states of (Kw's cos half, V) and (Kw's sin half, V)
+        for (int j = 0; j < 2; ++j) {
+            pre[j].Bm = (const char *)Kw + (size_t)j * DV * 2;
+            pre[j].lB = contiguous_layout(H, n, DK);
+            pre[j].states = (float *)workspace + j * set;
+            pre[j].act = LA_ACT_EXT;
+        }
+        rc = run_prepass(pre, 2, lams, scans, DV, LA_BF16, s);
+        // (the two sets lie one after the other: 2 B H scans of the same heads)
+        if (rc == LA_OK) rc = run_segment_scan<false>(l.r[0], lams, 2 * scans, DV, s);
+        if (rc != LA_OK) return rc;
+    }
+    hipLaunchKernelGGL(la_scan_bf16_dma_wide, dim3((unsigned)l.items), dim3(DmaWideCfg::NT), DmaWideCfg::lds_bytes,
+                       s, l, lams);
+    return hipGetLastError() == hipSuccess ? LA_OK : LA_ERR_LAUNCH;
+}
+
 }  // namespace
 
 extern "C" {
@@ -993,27 +1040,15 @@ int la_fwd_wide(const void *Qw, const void *Kw, const void *V, const float *lamb
     if (rc == LA_OK) rc = check_wide(dk, dv);
     if (rc != LA_OK) return rc;
     if (!Qw || !Kw) return LA_ERR_NULL;
-    // d_k = 256, d_v = 128 in bf16, whole sequences: one kernel with the 256 x 128 state
-    if (dt == LA_BF16 && dk == 256 && dv == 128 && make_plan(B, H, n, dv, dt).S == 1 &&
-        !g_sw.wide_slices.load(std::memory_order_relaxed)) {
-        if (!V || !O || !lambda) return LA_ERR_NULL;
-        if (!aligned16(Qw) || !aligned16(Kw) || !aligned16(V) || !aligned16(O)) return LA_ERR_ALIGN;
-        LaLambdas lams;
-        rc = check_lambda(lambda, H, &lams);
-        if (rc != LA_OK) return rc;
-        Plan p = make_plan(B, H, n, dv, dt);
-        ScanLaunch l = {};
-        l.r[0] = make_args(Qw, Kw, V, O, p, H, n, dv, dt, nullptr, 0);
-        l.nroles = 1; l.items = B * H;
-        auto kern = la_scan_bf16_dma_wide;
-        static std::once_flag once;
-        static hipError_t attr_err = hipSuccess;
-        std::call_once(once, [&] { attr_err = allow_lds(kern, DmaWideCfg::lds_bytes); });
-        if (attr_err != hipSuccess) return LA_ERR_LAUNCH;
-        hipLaunchKernelGGL(kern, dim3((unsigned)(B * H)), dim3(DmaWideCfg::NT), DmaWideCfg::lds_bytes,
-                           (hipStream_t)hip_stream, l, lams);
-        return hipGetLastError() == hipSuccess ? LA_OK : LA_ERR_LAUNCH;
-    }
+    // d_k = 256, d_v = 128 in bf16: one kernel with the 256 x 128 state.  Cut sequences run in S / 2 segments,
+    // whose states take the same scratch; with fewer than eight of the plan's segments the chains would get
+    // too long (short sequences: the accumulated scans' pieces).
+    const Plan plan = make_plan(B, H, n, dv, dt);
+    const bool cut_ok = plan.S >= 8 && 2L * B * H <= 65535 && !g_sw.staged_prepass.load(std::memory_order_relaxed) &&
+                        !g_sw.staged_scan.load(std::memory_order_relaxed);
+    if (dt == LA_BF16 && dk == 256 && dv == 128 && (plan.S == 1 || cut_ok) &&
+        !g_sw.wide_slices.load(std::memory_order_relaxed))
+        return forward_wide(Qw, Kw, V, lambda, O, plan, B, H, n, workspace, workspace_bytes, (hipStream_t)hip_stream);
     const size_t esz = dt == LA_BF16 ? 2 : 4;
     for (int j = 0; j < dk / dv; ++j) {
         Variant var;
