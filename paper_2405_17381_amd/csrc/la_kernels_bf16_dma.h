@@ -308,8 +308,6 @@ __global__ __launch_bounds__(2 * D_, NS_ <= 3 ? 2 : 1) void la_scan_bf16_dma(Sca
         for (int mt = 0; mt < MT_D; ++mt)
 #pragma unroll
             for (int v = 0; v < 16; ++v) st[mt][v] = p[(32 * mt + 8 * (v >> 2) + (v & 3)) * D];
-        __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0) here, or the compiler waits for them in the block
-                                                // loop, in every iteration, and for the tiles in flight too
     } else {
 #pragma unroll
         for (int mt = 0; mt < MT_D; ++mt)
@@ -381,6 +379,9 @@ __global__ __launch_bounds__(2 * D_, NS_ <= 3 ? 2 : 1) void la_scan_bf16_dma(Sca
 #pragma unroll
     for (int i = 0; i < PF; ++i)
         if (i < nblk) issue(i, i);
+    // vmcnt(0): the state loads land here, together with the first tiles, or the compiler would wait for
+    // them in the block loop, in every iteration, and for the tiles in flight too
+    if (has_init) __builtin_amdgcn_s_waitcnt(0x0f70);
     constexpr int ST = (ABL == 0 || ABL == 4) ? 2 : 0;           // store instructions per wave and block
 
     int stage = 0;
