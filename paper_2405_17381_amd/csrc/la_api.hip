@@ -242,17 +242,15 @@ hipError_t launch_bf16(const ScanLaunch &a, const LaLambdas &lams, hipStream_t s
 }
 
 // The backward pass's three block scans in one launch (see the kernel).
-template <bool STRIDED, int D = 128>
+template <bool STRIDED, int D = 128, bool EXTRA = false>
 hipError_t launch_bf16_dma_trio(const ScanLaunch &a, const LaLambdas &lams, hipStream_t s)
 {
-    using Cfg = DmaCfg<3, D>;
-    auto kern = la_scan_bf16_dma<false, true, 0, 3, true, STRIDED, D>;
-    static std::once_flag once;
-    static hipError_t attr_err = hipSuccess;
-    std::call_once(once, [&] { attr_err = allow_lds(kern, Cfg::lds_bytes); });
-    if (attr_err != hipSuccess) return attr_err;
+    constexpr int NS = EXTRA ? 2 : 3;
+    using Cfg = DmaCfg<NS, D>;
+    constexpr size_t lds = EXTRA ? Cfg::lds_bytes_e : Cfg::lds_bytes;
+    auto kern = la_scan_bf16_dma<false, true, 0, NS, true, STRIDED, D, false, EXTRA>;   // attributes: prepare_bf16
     dim3 grid(3u * (unsigned)((a.items + 7) / 8 * 8)), block(Cfg::NT);
-    hipLaunchKernelGGL(kern, grid, block, Cfg::lds_bytes, s, a, lams);
+    hipLaunchKernelGGL(kern, grid, block, lds, s, a, lams);
     return hipGetLastError();
 }
 
@@ -312,6 +310,10 @@ hipError_t prepare_bf16()
             allow_lds(la_scan_bf16_dma<false, true, 0, 3, true, true, D>, scan),
             allow_lds(la_scan_bf16_dma<false, true, 0, 3, false, true, D, true>, scan),
             allow_lds(la_scan_bf16_dma<false, true, 0, 3, true, true, D, true>, scan),
+            allow_lds(la_scan_bf16_dma<false, true, 0, 3, false, true, D, true, true>, scan),
+            allow_lds(la_scan_bf16_dma<false, true, 0, 2, false, true, D, true, true>, DmaCfg<2, D>::lds_bytes_e),
+            allow_lds(la_scan_bf16_dma<false, true, 0, 2, true, true, D, true, true>, DmaCfg<2, D>::lds_bytes_e),
+            allow_lds(la_scan_bf16_dma<false, true, 0, 2, true, true, D, false, true>, DmaCfg<2, D>::lds_bytes_e),
             allow_lds(la_prepass_bf16_dma<4, false, D>, pre), allow_lds(la_prepass_bf16_dma<4, true, D>, pre),
             allow_lds(la_prepass_bf16_tiles<false, D>, tiles), allow_lds(la_prepass_bf16_tiles<true, D>, tiles)};
         for (const hipError_t e : all)
@@ -406,15 +408,27 @@ hipError_t launch_f32s(const ScanLaunch &a, const LaLambdas &lams, hipStream_t s
 }
 
 // Block scans that rebuild their entering states: la_fwd's (one role) and la_bwd's (three).
-template <bool TRIO, int D>
+template <bool TRIO, int D, bool EXTRA, int NS>
 hipError_t launch_bf16_rebuild(const ScanLaunch &a, const LaLambdas &lams, hipStream_t s)
 {
-    using Cfg = DmaCfg<3, D>;
-    auto kern = la_scan_bf16_dma<false, true, 0, 3, TRIO, true, D, true>;   // attributes: prepare_bf16
+    using Cfg = DmaCfg<NS, D>;
+    constexpr size_t lds = NS == 2 ? Cfg::lds_bytes_e : Cfg::lds_bytes;
+    auto kern = la_scan_bf16_dma<false, true, 0, NS, TRIO, true, D, true, EXTRA>;       // attributes: prepare_bf16
     const unsigned items = (unsigned)a.items;
     dim3 grid(TRIO ? 3u * ((items + 7) / 8 * 8) : items), block(Cfg::NT);
-    hipLaunchKernelGGL(kern, grid, block, Cfg::lds_bytes, s, a, lams);
+    hipLaunchKernelGGL(kern, grid, block, lds, s, a, lams);
     return hipGetLastError();
+}
+
+template <int D>
+hipError_t launch_bf16_rebuild(const ScanLaunch &a, const LaLambdas &lams, hipStream_t s)
+{
+    int acts = 0;
+    for (int i = 0; i < a.nroles; ++i) acts |= a.r[i].act;
+    const bool extra = (acts & ~LA_ACT_EXT) != 0;
+    if (a.nroles == 3) return extra ? launch_bf16_rebuild<true, D, true, 2>(a, lams, s) : launch_bf16_rebuild<true, D, false, 3>(a, lams, s);
+    if (acts & (LA_ACT_OUT | LA_ACT_ACC)) return launch_bf16_rebuild<false, D, true, 2>(a, lams, s);
+    return extra ? launch_bf16_rebuild<false, D, true, 3>(a, lams, s) : launch_bf16_rebuild<false, D, false, 3>(a, lams, s);
 }
 
 // ... and in fp32.
@@ -432,8 +446,7 @@ hipError_t launch_f32_rebuild(const ScanLaunch &a, const LaLambdas &lams, hipStr
 hipError_t launch_rebuild(const ScanLaunch &a, const LaLambdas &lams, int d, la_dtype dt, hipStream_t s)
 {
     if (dt == LA_F32) return d == 64 ? launch_f32_rebuild<64>(a, lams, s) : launch_f32_rebuild<128>(a, lams, s);
-    if (a.nroles == 3) return d == 64 ? launch_bf16_rebuild<true, 64>(a, lams, s) : launch_bf16_rebuild<true, 128>(a, lams, s);
-    return d == 64 ? launch_bf16_rebuild<false, 64>(a, lams, s) : launch_bf16_rebuild<false, 128>(a, lams, s);
+    return d == 64 ? launch_bf16_rebuild<64>(a, lams, s) : launch_bf16_rebuild<128>(a, lams, s);
 }
 
 // bf16, direct-to-LDS family: plain launches and launches whose operands have their own layouts
@@ -457,8 +470,8 @@ hipError_t launch_bf16_direct(const ScanLaunch &a, const LaLambdas &lams, bool s
     return strided ? launch_bf16_dma<REV, true, D>(a, lams, s) : launch_bf16_dma<REV, false, D>(a, lams, s);
 }
 
-// bf16, register-staged family (64-row blocks): every activation / accumulation variant, and
-// everything when the "staged_scan" switch is set
+// bf16, register-staged family (64-row blocks): single scans and pre-passes with an activation or an
+// epilogue, and everything when the "staged_scan" switch is set
 template <bool REV, bool STATE_ONLY, int D>
 hipError_t launch_bf16_staged(const ScanLaunch &a, const LaLambdas &lams, bool ext, hipStream_t s)
 {
@@ -471,8 +484,10 @@ hipError_t launch_scan_kernel(const ScanLaunch &a, const LaLambdas &lams, int d,
                               la_dtype dt, hipStream_t s)
 {
     if (dt == LA_BF16) {
-        // LA_ACT_EXT alone: operands with their own layouts, nothing else; any other bit: an
-        // activation or an accumulating epilogue, which only the register-staged kernels carry
+        // LA_ACT_EXT alone: operands with their own layouts, nothing else; any other bit: an activation or
+        // an epilogue, which the direct-to-LDS kernels carry in pieces and in la_bwd's three-role launch
+        // only: one segmented forward scan is faster on the register-staged kernel (la_fwd_swish on 16 scans
+        // of 2048 tokens, d = 128: 56.0 against 59.1 us), as is the pre-pass.
         const int acts = a.r[0].act | a.r[a.nroles - 1].act;
         const bool plain = acts == 0 || acts == LA_ACT_EXT;
         const bool staged = !plain || g_sw.staged_scan.load(std::memory_order_relaxed) != 0 ||
@@ -667,10 +682,8 @@ int run_scan(const void *A, const void *Bm, const void *C, void *Out, const LaLa
     a.rev = REV ? 1 : 0;
     a.st_in = st_in;
     a.st_out = st_out;
-    // (the fp32 kernel takes pieces with any activation or epilogue)
-    const bool plain = dt == LA_F32 || a.act == 0 || a.act == LA_ACT_EXT;
     if (prepare(d, dt) != hipSuccess) return LA_ERR_LAUNCH;
-    const int piece = !REV && plain ? rebuild_piece(p, scans, H, n, d, dt, 1, lams, a.skip_bits) : 0;
+    const int piece = !REV ? rebuild_piece(p, scans, H, n, d, dt, 1, lams, a.skip_bits) : 0;
     if (piece > 0) {
         ScanLaunch l = {};
         l.saved = p.S > 1 ? a.states : nullptr;              // for la_bwd_saved
@@ -758,7 +771,7 @@ int run_backward(const void *Q, const void *K, const void *V, const void *dO, vo
     const int acts = pre[0].act | pre[1].act | av.act;
     const bool all_ext = pre[0].act == LA_ACT_EXT && pre[1].act == LA_ACT_EXT && av.act == LA_ACT_EXT;
     if (prepare(d, dt) != hipSuccess) return LA_ERR_LAUNCH;
-    const int piece = !reuse && (dt == LA_F32 || acts == 0 || all_ext) ? rebuild_piece(p, scans, H, n, d, dt, 3, lams, av.skip_bits) : 0;
+    const int piece = !reuse ? rebuild_piece(p, scans, H, n, d, dt, 3, lams, av.skip_bits) : 0;
     if (piece > 0) {
         ScanLaunch l = {};
         l.r[0] = pre[0]; l.r[1] = pre[1]; l.r[2] = av; l.nroles = 3;
@@ -779,7 +792,7 @@ int run_backward(const void *Q, const void *K, const void *V, const void *dO, vo
         if (rc != LA_OK) return rc;
     }
     const bool one_launch = !g_sw.no_trio.load(std::memory_order_relaxed) && !g_sw.no_pair.load(std::memory_order_relaxed) &&
-        (dt == LA_BF16 ? (acts == 0 || all_ext) && !g_sw.staged_scan.load(std::memory_order_relaxed) &&
+        (dt == LA_BF16 ? !g_sw.staged_scan.load(std::memory_order_relaxed) &&
                              !g_sw.ablate.load(std::memory_order_relaxed)
                        : !g_sw.f32_plain.load(std::memory_order_relaxed));
     if (one_launch) {
@@ -788,6 +801,8 @@ int run_backward(const void *Q, const void *K, const void *V, const void *dO, vo
         ScopedTimer t(s);
         hipError_t e;
         if (dt == LA_F32) e = d == 64 ? launch_f32s<64, false>(l, lams, s) : launch_f32s<128, false>(l, lams, s);
+        else if (acts != 0 && !all_ext) e = d == 64 ? launch_bf16_dma_trio<true, 64, true>(l, lams, s)
+                                                    : launch_bf16_dma_trio<true, 128, true>(l, lams, s);
         else if (d == 64) e = all_ext ? launch_bf16_dma_trio<true, 64>(l, lams, s) : launch_bf16_dma_trio<false, 64>(l, lams, s);
         else e = all_ext ? launch_bf16_dma_trio<true>(l, lams, s) : launch_bf16_dma_trio<false>(l, lams, s);
         return e == hipSuccess ? LA_OK : LA_ERR_LAUNCH;

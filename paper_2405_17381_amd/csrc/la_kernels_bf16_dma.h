@@ -78,6 +78,10 @@ struct DmaCfg {
     static constexpr int STAGE_BYTES = NTILE * TILE_BYTES;
     static constexpr int SO_BYTES = BK * D * 2;              // the Out tile, bf16
     static constexpr size_t lds_bytes = (size_t)NS * STAGE_BYTES + SO_BYTES;   // 81920 at NS = 3, D = 128
+    static constexpr int E_OFF = NS * STAGE_BYTES + SO_BYTES;                  // epilogue tile (EXTRA, NS = 2)
+    // 65536 at NS = 2, D = 128, and room for a state to be transposed ([D][D + 1] floats)
+    static constexpr size_t state_bytes = (size_t)D * (D + 1) * 4;
+    static constexpr size_t lds_bytes_e = lds_bytes + SO_BYTES > state_bytes ? lds_bytes + SO_BYTES : state_bytes;
 };
 
 // Chunk swizzle of a tile row (see the layout note above).  D = 128: the low four bits of r
@@ -156,8 +160,19 @@ __device__ __forceinline__ U2 lds_read_tr(const unsigned char *p)
 //   so that no pre-pass and no segment scan run first and pieces may be shorter than what segment
 //   states in scratch would allow.  ScanArgs::L is the piece, S the pieces per scan, `states` unused;
 //   ScanLaunch::saved (if any) receives the states at multiples of saved_L, as the segment scan leaves them.
+// EXTRA: operands may be pre-activations and the result may take an epilogue (ScanArgs::act).
+//   Activation.  A lane applies Swish in place to the 16-byte pieces that its own direct loads
+//   brought, between their landing and the block's barrier: no extra barrier, each element once per
+//   workgroup.  It makes these launches vector-bound: two transcendentals an element, 1700 cycles a wave
+//   and block where two tiles are activated; without them they would take three quarters of the time.
+//   Epilogue, with NS = 2 only: the tile whose phi' scales Out, or the previous Out to add to, comes
+//   by direct loads of the same form as the result stores, so that every lane finds the piece it needs
+//   where its own load put it and waits for that load alone.  Its 8 KB take the place of the third
+//   stage.  Against a paired and a single launch of the register-staged kernels, la_bwd_swish, us: 16 scans of
+//   2048 tokens at d = 128 96 -> 68, 16 of 1000 92 -> 64 (in pieces 49); forward and
+//   backward of 64 scans of 8192, where arithmetic bounds both, 617 -> 608 (four runs: 0.4 to 1.5 % faster).
 template <bool REV_, bool NT_STORE, int ABL, int NS_, bool TRIO = false, bool STRIDED = false, int D_ = 128,
-          bool REBUILD = false>
+          bool REBUILD = false, bool EXTRA = false>
 __global__ __launch_bounds__(2 * D_, NS_ <= 3 ? 2 : 1) void la_scan_bf16_dma(ScanLaunch launch, LaLambdas lams)
 {
     using Cfg = DmaCfg<NS_, D_>;
@@ -240,6 +255,17 @@ __global__ __launch_bounds__(2 * D_, NS_ <= 3 ? 2 : 1) void la_scan_bf16_dma(Sca
         gT[2] = (const uint16_t *)a.C + base;
         gO = (uint16_t *)a.Out + base;
         ldT[0] = ldT[1] = ldT[2] = ldO = D;
+    }
+
+    // operands to activate, and the epilogue tile with its row distance
+    const int act = EXTRA ? a.act : 0;
+    const bool has_e = EXTRA && NS == 2 && (act & (LA_ACT_OUT | LA_ACT_ACC)) != 0;
+    const uint16_t *gE = gO;
+    int ldE = ldO;
+    if (EXTRA && (act & LA_ACT_OUT)) {
+        const long bb = scan / a.H, hh = scan % a.H;
+        gE = (const uint16_t *)a.E + bb * a.lE.bs + hh * a.lE.hs;
+        ldE = a.lE.ld;
     }
 
     // ---- per-lane constants ----------------------------------------------------------
@@ -344,6 +370,15 @@ __global__ __launch_bounds__(2 * D_, NS_ <= 3 ? 2 : 1) void la_scan_bf16_dma(Sca
             }
         }
     };
+    // ---- epilogue tile of one block: the very pieces store_out handles in this lane
+    auto issue_e = [&](int t0) {
+        const int last = min(BK, seg_hi - t0) - 1;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const int row = min(2 * RPI * w + RPI * p + l / CPR, last);
+            dma_load16<false>(gE + (size_t)(t0 + row) * ldE + 8 * (l % CPR), lds0 + Cfg::E_OFF + (2 * w + p) * 1024);
+        }
+    };
     // ---- Out tile: LDS -> memory, 8 whole rows per wave.  Always two store instructions
     // with every lane active (see the note on counting above): a row past the end of the
     // sequence stores the last real row again.
@@ -353,7 +388,11 @@ __global__ __launch_bounds__(2 * D_, NS_ <= 3 ? 2 : 1) void la_scan_bf16_dma(Sca
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
             const int row = min(2 * RPI * w + RPI * p + l / CPR, last), ch = l % CPR;
-            const U4 o = *(const U4 *)(sO + row * PITCH + ((ch ^ (row & (CPR - 1))) << 4));
+            U4 o = *(const U4 *)(sO + row * PITCH + ((ch ^ (row & (CPR - 1))) << 4));
+            if (has_e) {
+                const U4 e = *(const U4 *)(smem_dma + Cfg::E_OFF + (2 * w + p) * 1024 + 16 * l);
+                o = (act & LA_ACT_OUT) ? mul_swish_grad_u4(o, e) : add_u4(o, e);
+            }
             U4 *dst = (U4 *)(gO + (size_t)(t0 + row) * ldO + 8 * ch);
             if (NT_STORE) __builtin_nontemporal_store(o, dst);
             else *dst = o;
@@ -383,6 +422,10 @@ __global__ __launch_bounds__(2 * D_, NS_ <= 3 ? 2 : 1) void la_scan_bf16_dma(Sca
     // them in the block loop, in every iteration, and for the tiles in flight too
     if (has_init) __builtin_amdgcn_s_waitcnt(0x0f70);
     constexpr int ST = (ABL == 0 || ABL == 4) ? 2 : 0;           // store instructions per wave and block
+    // blocks whose stores may be in flight at a block's wait: its loads went out in iteration ib - PF, before
+    // that iteration's stores, so PF of them; with two blocks of prefetch one fewer costs nothing (measured
+    // level), with one (EXTRA's two stages) the wait would be for the stores just issued
+    constexpr int SB = EXTRA ? PF : PF - 1;
 
     int stage = 0;
     for (int ib = 0; ib < nblk; ++ib) {
@@ -397,13 +440,16 @@ __global__ __launch_bounds__(2 * D_, NS_ <= 3 ? 2 : 1) void la_scan_bf16_dma(Sca
         const bool warm = REBUILD && ib < nwarm;
         if (REBUILD) {                          // a leading block loads two tiles and stores nothing
             const int young = min(PF - 1, nblk - 1 - ib), lead = max(0, min(young, nwarm - 1 - ib));
-            la_wait_vm_le<(PF - 1) * (LOADS + ST)>(LOADS * young - SPW * lead + ST * min(PF - 1, max(0, ib - nwarm)));
+            la_wait_vm_le<(PF - 1) * (LOADS + 2 * EXTRA) + SB * ST>(LOADS * young - SPW * lead + ST * min(SB, max(0, ib - nwarm)) +
+                                                                (has_e ? 2 * min(PF - 1, max(0, ib - nwarm)) : 0));
         } else if (nblk < 2 * PF + 1 || ib + 1 >= nblk) {
             la_wait_vm<0>();
         } else {
+            // (an epilogue's two loads a block go out just before the loads of block ib + PF)
             const int young = min(PF - 1, nblk - 1 - ib);    // blocks whose loads are younger
-            const int olds = min(PF - 1, ib);                // blocks whose stores are younger
-            la_wait_vm_le<(PF - 1) * (LOADS + ST)>(LOADS * young + ST * olds);
+            const int olds = min(SB, ib);                    // blocks whose stores are younger
+            la_wait_vm_le<(PF - 1) * (LOADS + 2 * EXTRA) + SB * ST>(LOADS * young + ST * olds +
+                                                                (has_e ? 2 * min(PF - 1, ib) : 0));
         }
         if (t0 + BK > seg_hi) {                 // partial block: zero padding (exact)
             const U4 z = {0u, 0u, 0u, 0u};
@@ -424,8 +470,21 @@ __global__ __launch_bounds__(2 * D_, NS_ <= 3 ? 2 : 1) void la_scan_bf16_dma(Sca
                 lamBK = pw(m);
             }
         }
+        if (EXTRA && (act & (LA_ACT_A | LA_ACT_BM | LA_ACT_C))) {
+            // (phi(0) = 0: the padding stays zero)
+#pragma unroll
+            for (int t = 0; t < NTILE; ++t)
+                if ((act & (t == 0 ? LA_ACT_A : t == 1 ? LA_ACT_BM : LA_ACT_C)) && !(t == 0 && warm)) {
+#pragma unroll
+                    for (int j = 0; j < SPW; ++j) {
+                        U4 *p = (U4 *)(sb + t * Cfg::TILE_BYTES + (SPW * w + j) * 1024 + 16 * l);
+                        *p = swish_u4(*p);
+                    }
+                }
+        }
         LA_LDS_BARRIER();                       // the block has landed for every wave; the stage
                                                 // of block ib - 1 is free for block ib + PF
+        if (has_e && !warm) issue_e(t0);
         if (ib + PF < nblk) issue(ib + PF, stage >= 1 ? stage - 1 : NS - 1);
 
         if (ABL == 2 || ABL == 4) {
@@ -531,6 +590,10 @@ __global__ __launch_bounds__(2 * D_, NS_ <= 3 ? 2 : 1) void la_scan_bf16_dma(Sca
         }
         if (!warm) {
             LA_LDS_BARRIER();                   // the Out tile is complete
+            if (has_e) {                        // only the next block's loads are younger than the epilogue's
+                if (ib + PF < nblk) la_wait_vm<LOADS>();
+                else la_wait_vm<0>();
+            }
             store_out(t0);
         }
         stage = stage + 1 < NS ? stage + 1 : 0;
